@@ -3,8 +3,10 @@
 //
 // This file holds the partial-pivoting form (GEPP); static block pivoting
 // lives in lu_tiles.hip.  Right-looking blocked algorithm with panel width kNb:
-//   panel   : one workgroup factors the n-k x jb panel (pivot search over the
-//             whole column);
+//   panel   : the n-k x jb panel is factored with pivot search over the whole
+//             column: up to 8192 rows in the registers of one workgroup
+//             (lu_panel.hip), above that over many workgroups with one
+//             grid-wide barrier per column;
 //   swap    : one wavefront per column applies the panel's row interchanges
 //             (lanes hold the jb pivot rows, interchanges with rows below the
 //             panel are resolved in registers) and, right of the panel, solves
@@ -120,9 +122,7 @@ constexpr int64_t kCoopSpin = 1 << 24;
 
 template <class T>
 inline int64_t coop_rows(int64_t m) {
-  // all rows in one workgroup when they fit in 120 KiB of LDS (no grid-wide
-  // barrier at all), else at least 64 rows and at most kCoopMaxG workgroups
-  if (m * kNb * (int64_t)sizeof(T) <= 120 * 1024) return m;
+  // at least 64 rows per workgroup and at most kCoopMaxG workgroups
   return std::max<int64_t>(64, (m + kCoopMaxG - 1) / kCoopMaxG);
 }
 
@@ -188,94 +188,79 @@ __global__ __launch_bounds__(kCoopThreads) void k_getf2_coop(int64_t n, int64_t 
       s_p = bi;
     }
     __syncthreads();
-    if (G == 1) {
-      // one workgroup holds every row: the pivot is the local one
-      const int64_t p = s_p;
-      if (tid < jb) {
-        s_prow[tid] = P[tid * R + (p - r0)];
-        s_top[tid] = P[tid * R + (gj - r0)];
+    const int64_t mine = s_p;
+    if (tid < jb) {
+      slot[2 + tid] = (mine >= r0 && mine < r0 + nr) ? (double)P[tid * R + (mine - r0)] : 0.0;
+      if (gj >= r0 && gj < r0 + nr) top[2 + tid] = (double)P[tid * R + (gj - r0)];
+    }
+    // grid-wide barrier (bounded wait; a timeout raises bit 1 of the
+    // singular flag and the launch still completes)
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      const int32_t target = (j + 1) * G;
+      atomicAdd(bar, 1);
+      int64_t spins = 0;
+      while (__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+        __builtin_amdgcn_s_sleep(1);
+        if (++spins > kCoopSpin) {
+          atomicOr(sing, 2);
+          break;
+        }
       }
-      if (tid == 0) ipiv[gj] = (int32_t)p;
-      __syncthreads();
-      if (p != gj && tid < jb) {
-        P[tid * R + (p - r0)] = s_top[tid];
-        P[tid * R + (gj - r0)] = s_prow[tid];
-      }
-    } else {
-      const int64_t mine = s_p;
-      if (tid < jb) {
-        slot[2 + tid] = (mine >= r0 && mine < r0 + nr) ? (double)P[tid * R + (mine - r0)] : 0.0;
-        if (gj >= r0 && gj < r0 + nr) top[2 + tid] = (double)P[tid * R + (gj - r0)];
-      }
-      // grid-wide barrier (bounded wait; a timeout raises bit 1 of the
-      // singular flag and the launch still completes)
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      if (tid == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        const int32_t target = (j + 1) * G;
-        atomicAdd(bar, 1);
-        int64_t spins = 0;
-        while (__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-          __builtin_amdgcn_s_sleep(1);
-          if (++spins > kCoopSpin) {
-            atomicOr(sing, 2);
-            break;
-          }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        __builtin_amdgcn_s_waitcnt(0);
+    }
+    __syncthreads();
+    // the pivot: the candidates reduced in the same order by every
+    // workgroup; the diagonal row is fetched in the same round
+    const double* cand = slots + (size_t)((j & 1) * kCoopMaxG) * kSlot;
+    if (tid >= kCoopThreads - 64 && tid - (kCoopThreads - 64) < jb)
+      s_top[tid - (kCoopThreads - 64)] = (T)__hip_atomic_load(
+          &top[2 + tid - (kCoopThreads - 64)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    best = -1.0;
+    bi = n;
+    for (int q = tid; q < G; q += kCoopThreads) {
+      const double v = __hip_atomic_load(&cand[(size_t)q * kSlot], __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+      const int64_t i = (int64_t)__hip_atomic_load(&cand[(size_t)q * kSlot + 1],
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (v > best || (v == best && i < bi)) {
+        best = v;
+        bi = i;
       }
-      __syncthreads();
-      // the pivot: the candidates reduced in the same order by every
-      // workgroup; the diagonal row is fetched in the same round
-      const double* cand = slots + (size_t)((j & 1) * kCoopMaxG) * kSlot;
-      if (tid >= kCoopThreads - 64 && tid - (kCoopThreads - 64) < jb)
-        s_top[tid - (kCoopThreads - 64)] = (T)__hip_atomic_load(
-            &top[2 + tid - (kCoopThreads - 64)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      best = -1.0;
-      bi = n;
-      for (int q = tid; q < G; q += kCoopThreads) {
-        const double v = __hip_atomic_load(&cand[(size_t)q * kSlot], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-        const int64_t i = (int64_t)__hip_atomic_load(&cand[(size_t)q * kSlot + 1],
-                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (v > best || (v == best && i < bi)) {
-          best = v;
-          bi = i;
-        }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      const double ov = __shfl_xor(best, off);
+      const int64_t oi = __shfl_xor(bi, off);
+      if (ov > best || (ov == best && oi < bi)) {
+        best = ov;
+        bi = oi;
       }
-      for (int off = 32; off > 0; off >>= 1) {
-        const double ov = __shfl_xor(best, off);
-        const int64_t oi = __shfl_xor(bi, off);
-        if (ov > best || (ov == best && oi < bi)) {
-          best = ov;
-          bi = oi;
-        }
-      }
-      if (lane == 0) {
-        s_v[wid] = best;
-        s_i[wid] = bi;
-      }
-      __syncthreads();
-      if (tid == 0) {
-        int wbest = 0;
-        for (int w = 1; w < kCoopThreads / 64; ++w)
-          if (s_v[w] > s_v[wbest] || (s_v[w] == s_v[wbest] && s_i[w] < s_i[wbest])) wbest = w;
-        s_p = s_i[wbest];
-      }
-      __syncthreads();
-      const int64_t p = s_p;
-      const int pw = (int)((p - k) / R);   // the workgroup whose rows hold row p
-      if (tid < jb)
-        s_prow[tid] = (T)__hip_atomic_load(&cand[(size_t)pw * kSlot + 2 + tid], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-      if (g == 0 && tid == 0) ipiv[gj] = (int32_t)p;
-      __syncthreads();
-      if (p != gj && tid < jb) {
-        if (p >= r0 && p < r0 + nr) P[tid * R + (p - r0)] = s_top[tid];
-        if (gj >= r0 && gj < r0 + nr) P[tid * R + (gj - r0)] = s_prow[tid];
-      }
+    }
+    if (lane == 0) {
+      s_v[wid] = best;
+      s_i[wid] = bi;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      int wbest = 0;
+      for (int w = 1; w < kCoopThreads / 64; ++w)
+        if (s_v[w] > s_v[wbest] || (s_v[w] == s_v[wbest] && s_i[w] < s_i[wbest])) wbest = w;
+      s_p = s_i[wbest];
+    }
+    __syncthreads();
+    const int64_t p = s_p;
+    const int pw = (int)((p - k) / R);   // the workgroup whose rows hold row p
+    if (tid < jb)
+      s_prow[tid] = (T)__hip_atomic_load(&cand[(size_t)pw * kSlot + 2 + tid], __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+    if (g == 0 && tid == 0) ipiv[gj] = (int32_t)p;
+    __syncthreads();
+    if (p != gj && tid < jb) {
+      if (p >= r0 && p < r0 + nr) P[tid * R + (p - r0)] = s_top[tid];
+      if (gj >= r0 && gj < r0 + nr) P[tid * R + (gj - r0)] = s_prow[tid];
     }
     __syncthreads();
     const T piv = s_prow[j];
@@ -298,76 +283,90 @@ __global__ __launch_bounds__(kCoopThreads) void k_getf2_coop(int64_t n, int64_t 
     for (int r = lane; r < nr; r += 64) A[(r0 + r) + (k + c) * lda] = P[c * R + r];
 }
 
+template <class T>
+__device__ inline T bcast_lane(T v, int lane);
+template <>
+__device__ inline float bcast_lane<float>(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+template <>
+__device__ inline double bcast_lane<double>(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
 // Columns handled: [0, k) (interchanges only), [k+jb, n) (interchanges and
 // the unit-lower solve for U12), and the permutation column (interchanges
-// only): one wavefront per column.
+// only); with sub > 0 instead the panel's own columns, each with the
+// interchanges of the sub-panels (sub columns each) after its own: one
+// wavefront per column.
 template <class T>
-__global__ __launch_bounds__(256) void k_laswp_trsm(int64_t n, int64_t k, int jb,
+__global__ __launch_bounds__(256) void k_laswp_trsm(int64_t n, int64_t k, int jb, int sub,
                                                     T* __restrict__ A, int64_t lda,
                                                     const int32_t* __restrict__ ipiv,
                                                     int32_t* __restrict__ perm) {
   __shared__ T sL[kNb * kNb];
-  __shared__ int32_t sp[kNb];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (threadIdx.x < jb) sp[threadIdx.x] = ipiv[k + threadIdx.x];
-  for (int e = threadIdx.x; e < jb * jb; e += 256) {
-    const int r = e % jb, c = e / jb;
-    sL[e] = A[(k + r) + (k + c) * lda];
+  const int64_t nleft = k, nright = sub > 0 ? 0 : n - k - jb;
+  const int64_t c0 = blockIdx.x * (int64_t)4;
+  if (nright > 0 && c0 + 3 >= nleft) {
+    for (int e = threadIdx.x; e < jb * jb; e += 256) {
+      const int r = e % jb, c = e / jb;
+      sL[e] = A[(k + r) + (k + c) * lda];
+    }
   }
   __syncthreads();
-  const int64_t nleft = k, nright = n - k - jb;
-  const int64_t cid = blockIdx.x * 4 + w;
-  if (cid > nleft + nright) return;
-  const bool is_perm = cid == nleft + nright;
-  const bool solve = !is_perm && cid >= nleft;
+  const int64_t cid = c0 + w;
+  const bool is_perm = sub == 0 && cid == nleft + nright;
+  if (sub > 0 ? cid >= jb : cid > nleft + nright) return;
+  const bool solve = sub == 0 && !is_perm && cid >= nleft;
+  const int first = sub > 0 ? (int)(cid / sub + 1) * sub : 0;   // first interchange
   T* col = nullptr;
-  if (!is_perm) col = A + (cid < nleft ? cid : cid + jb) * lda;
-  const int64_t kend = k + jb;
+  if (!is_perm) col = A + (sub > 0 ? k + cid : (cid < nleft ? cid : cid + jb)) * lda;
   const bool mine = lane < jb;
+  const int pl = mine ? (int)(ipiv[k + lane] - k) : -1;   // relative to the panel's first row
+  const bool outside = mine && lane >= first && pl >= jb;
+  bool final_w = outside;
   T reg = T(0), slot = T(0), outval = T(0);
-  int64_t pl = -1;
-  bool outside = false, final_w = false;
   if (mine) {
-    pl = sp[lane];
-    outside = pl >= kend;
-    final_w = outside;
     reg = is_perm ? (T)perm[k + lane] : col[k + lane];
-    if (outside) slot = is_perm ? (T)perm[pl] : col[pl];
+    if (outside) slot = is_perm ? (T)perm[k + pl] : col[k + pl];
   }
-  for (int j = 0; j < jb; ++j) {
-    const int64_t p = sp[j];
-    if (p < kend) {
-      const int pj = (int)(p - k);
-      if (pj != j) {
-        const T a = __shfl(reg, j);
-        const T b = __shfl(reg, pj);
+  for (int j = first; j < jb; ++j) {
+    const int p = __builtin_amdgcn_readlane(pl, j);
+    const T a = bcast_lane(reg, j);
+    if (p < jb) {
+      if (p != j) {
+        const T b = bcast_lane(reg, p);
         if (lane == j) reg = b;
-        if (lane == pj) reg = a;
+        if (lane == p) reg = a;
       }
     } else {
-      const T a = __shfl(reg, j);
-      const T b = __shfl(slot, j);
+      const T b = bcast_lane(slot, j);
       if (lane == j) {
         reg = b;
         outval = a;
       }
-      if (mine && lane > j && pl == p) slot = a;
-      if (mine && lane < j && pl == p) final_w = false;
+      if (lane > j && pl == p) slot = a;
+      if (lane < j && pl == p) final_w = false;
     }
   }
   if (solve) {
+#pragma unroll 8
     for (int t = 0; t < jb; ++t) {
-      const T xt = __shfl(reg, t);
+      const T xt = bcast_lane(reg, t);
       if (mine && lane > t) reg -= sL[lane + t * jb] * xt;
     }
   }
   if (mine) {
     if (is_perm) {
       perm[k + lane] = (int32_t)reg;
-      if (final_w) perm[pl] = (int32_t)outval;
+      if (final_w) perm[k + pl] = (int32_t)outval;
     } else {
       col[k + lane] = reg;
-      if (final_w) col[pl] = outval;
+      if (final_w) col[k + pl] = outval;
     }
   }
 }
@@ -596,20 +595,6 @@ __device__ inline int32_t ld_relaxed(const int32_t* p) {
 }
 __device__ inline void st_release(int32_t* p, int32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-template <class T>
-__device__ inline T bcast_lane(T v, int lane);
-template <>
-__device__ inline float bcast_lane<float>(float v, int lane) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-template <>
-__device__ inline double bcast_lane<double>(double v, int lane) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
 // LOCALP: the factors come from the tile LU with static block pivoting; the
@@ -1069,12 +1054,17 @@ size_t gepp_scratch_bytes(int64_t n) {
 
 namespace {
 
-// Panel of columns k .. k+jb-1 over rows k .. n-1: spread over workgroups
-// (cooperative launch) when its rows fit their LDS, else one workgroup.
+// Panel of columns k .. k+jb-1 over rows k .. n-1: in the registers of one
+// workgroup up to 8192 rows (FP64 factorisation of order 1000 6.2 -> 2.7 ms,
+// 2500 17.6 -> 8.0, 4500 37.5 -> 19.3, 8000 86.0 -> 56.5 against the form with a
+// grid-wide barrier per column, which is left for more rows), else spread over
+// workgroups (cooperative launch) when the rows fit their LDS, else one workgroup
+// on memory.
 template <class T>
 hipError_t launch_panel(int64_t n, int64_t k, int jb, T* A, int64_t lda, int32_t* ipiv,
                         int32_t* sing, void* scratch, hipStream_t s) {
   int64_t m = n - k;
+  if (panel_reg_width(m) > 0) return launch_panel_reg<T>(n, k, jb, A, lda, ipiv, sing, s);
   int64_t R = coop_rows<T>(m);
   const size_t lds = (size_t)R * kNb * sizeof(T);
   if (scratch && lds <= 128 * 1024) {
@@ -1082,11 +1072,6 @@ hipError_t launch_panel(int64_t n, int64_t k, int jb, T* A, int64_t lda, int32_t
     int32_t* bar =
         reinterpret_cast<int32_t*>(slots + (size_t)(2 * kCoopMaxG + 2) * kSlot) + k / kNb;
     const unsigned G = (unsigned)((m + R - 1) / R);
-    if (G == 1) {  // one workgroup: no co-residency to guarantee
-      hipLaunchKernelGGL(k_getf2_coop<T>, dim3(1), dim3(kCoopThreads), (unsigned)lds, s, n, k, jb,
-                         R, A, lda, ipiv, sing, slots, bar);
-      return hipGetLastError();
-    }
     void* args[] = {&n, &k, &jb, &R, &A, &lda, &ipiv, &sing, &slots, &bar};
     return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_getf2_coop<T>), dim3(G),
                                       dim3(kCoopThreads), args, (unsigned)lds, s);
@@ -1115,9 +1100,13 @@ hipError_t launch_lu_factor(int64_t n, T* A, int64_t lda, int32_t* ipiv, int32_t
     const int jb = (int)std::min<int64_t>(kNb, n - k);
     hipError_t e = launch_panel<T>(n, k, jb, A, lda, ipiv, sing, scratch, s);
     if (e != hipSuccess) return e;
+    const int sub = panel_reg_width(n - k);
+    if (sub > 0 && sub < jb)
+      hipLaunchKernelGGL(k_laswp_trsm<T>, dim3((unsigned)((jb + 3) / 4)), dim3(256), 0, s, n, k,
+                         jb, sub, A, lda, ipiv, perm);
     const int64_t ncols = (n - jb) + 1;
     hipLaunchKernelGGL(k_laswp_trsm<T>, dim3((unsigned)((ncols + 3) / 4)), dim3(256), 0, s, n, k,
-                       jb, A, lda, ipiv, perm);
+                       jb, 0, A, lda, ipiv, perm);
     const int64_t rest = n - k - jb;
     if (rest > 0) {
       dim3 g((unsigned)((rest + kGT - 1) / kGT), (unsigned)((rest + kGT - 1) / kGT));

@@ -439,6 +439,12 @@ hipError_t launch_apply(const nrs_problem& pb, const Sorted& srt, const double* 
 template <class T>
 hipError_t launch_lu_factor(int64_t n, T* A, int64_t lda, int32_t* ipiv, int32_t* perm,
                             int32_t* sing, hipStream_t s, void* scratch = nullptr);
+// Panel k .. k+jb-1 with its rows in registers (lu_panel.hip): sub-panels of
+// panel_reg_width(n - k) columns, 0 if the rows do not fit.
+int panel_reg_width(int64_t m);
+template <class T>
+hipError_t launch_panel_reg(int64_t n, int64_t k, int jb, T* A, int64_t lda, int32_t* ipiv,
+                            int32_t* sing, hipStream_t s);
 // bytes of the GEPP panel scratch (candidate rows, barrier counters) for order n
 size_t gepp_scratch_bytes(int64_t n);
 // Factor with scope 0 (GEPP, lu.hip) or 1 (tile LU with static block

@@ -1,0 +1,109 @@
+"""Partial-pivoting LU whose panel rows are held in registers: every rows-per-
+thread / width shape at both ends of its range, against LAPACK's pivots and the
+backward error bound of Gaussian elimination."""
+import numpy as np
+import pytest
+import scipy.linalg
+import torch
+
+import paper_2001_06468_amd as nrs
+from gpu_util import DEV, lu_ws
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    return nrs.Context(0)
+
+
+def _factor(ctx, A0, dtype, pad=0):
+    n = A0.shape[0]
+    lda = n + pad
+    A = torch.zeros((n, lda), dtype=dtype, device=DEV)
+    A[:, :n] = torch.from_numpy(np.ascontiguousarray(A0.T)).to(DEV, dtype)
+    ipiv = torch.empty(n, dtype=torch.int32, device=DEV)
+    perm = torch.empty(n, dtype=torch.int32, device=DEV)
+    sing = torch.zeros(1, dtype=torch.int32, device=DEV)
+    nrs.nrs_lu_factor(ctx, A, lda, ipiv, perm, sing, lu_ws(ctx, n, A))
+    return A[:, :n].T, ipiv.cpu().numpy(), perm.long(), int(sing.item())
+
+
+def _backward_ok(A0, LU, perm, unit):
+    """|P A - L U| <= gamma_n |L| |U| entry by entry (Higham, Theorem 9.3), the
+    check's own product in FP64 adding at most as much again."""
+    n = A0.shape[0]
+    LU = LU.double()
+    L = torch.tril(LU, -1) + torch.eye(n, dtype=torch.float64, device=DEV)
+    U = torch.triu(LU)
+    A = torch.from_numpy(A0).to(DEV).double()[perm]
+    gamma = n * unit / (1 - n * unit)
+    bound = 2 * gamma * (L.abs() @ U.abs().contiguous())
+    return bool(((A - L @ U).abs() <= bound).all())
+
+
+# rows a panel may have per shape: 512, 1024, 1536, 2048, 3072, 4096, 8192
+@pytest.mark.parametrize("n", [2, 16, 17, 80, 512, 513, 1025, 1537, 2049, 3073, 4097, 8193])
+def test_panel_shapes_fp64(ctx, n):
+    rng = np.random.default_rng(n)
+    A0 = rng.normal(size=(n, n))
+    LU, ipiv, perm, sing = _factor(ctx, A0, torch.float64, pad=n % 3)
+    assert sing == 0
+    np.testing.assert_array_equal(ipiv, scipy.linalg.lu_factor(A0)[1])
+    assert _backward_ok(A0, LU, perm, 2.0 ** -53)
+
+
+@pytest.mark.parametrize("n", [3, 65, 513, 1537, 2049])
+def test_panel_shapes_fp32(ctx, n):
+    rng = np.random.default_rng(n)
+    A0 = rng.normal(size=(n, n)).astype(np.float32)
+    LU, _, perm, sing = _factor(ctx, A0, torch.float32, pad=1)
+    assert sing == 0
+    assert _backward_ok(A0, LU, perm, 2.0 ** -24)
+
+
+def test_panel_exact_ties_and_swapped_rows(ctx):
+    """Entries +-1 and 0 tie all the time (lowest row wins), small integers keep
+    every product exact until the first division; a permutation matrix moves
+    every row."""
+    rng = np.random.default_rng(5)
+    n = 600
+    T0 = np.eye(n)[rng.permutation(n)]
+    LU, ipiv, perm, sing = _factor(ctx, T0, torch.float64)
+    assert sing == 0
+    np.testing.assert_array_equal(ipiv, scipy.linalg.lu_factor(T0)[1])
+    np.testing.assert_array_equal(LU.cpu().numpy(), np.eye(n))
+    # first column all +-1: the pivot is row 0, then rows tie again
+    S0 = rng.choice([-1.0, 1.0], size=(40, 40)) * 2.0 ** rng.integers(0, 2, size=(40, 40))
+    LU, ipiv, perm, sing = _factor(ctx, S0, torch.float64)
+    assert ipiv[0] == int(np.argmax(np.abs(S0[:, 0])))
+    assert _backward_ok(S0, LU, perm, 2.0 ** -53)
+
+
+@pytest.mark.parametrize("cols", [[0], [5, 15, 16], [63], [40, 64, 69]])
+def test_panel_zero_columns(ctx, cols):
+    """A zero column keeps its diagonal row, raises the flag and leaves the rest of
+    the elimination as LAPACK does it."""
+    n = 70
+    A0 = np.random.default_rng(7).normal(size=(n, n))
+    A0[:, cols] = 0.0
+    LU, ipiv, perm, sing = _factor(ctx, A0, torch.float64)
+    assert sing == 1
+    import warnings
+    with warnings.catch_warnings():
+        warnings.simplefilter("ignore")
+        _, ref = scipy.linalg.lu_factor(A0)
+    np.testing.assert_array_equal(ipiv, ref)
+    assert _backward_ok(A0, LU, perm, 2.0 ** -53)
+
+
+def test_panel_nan_column_stays_in_range(ctx):
+    """Columns without a finite entry: every interchange stays inside the matrix,
+    the entries before the first such column are finite."""
+    n = 130
+    A0 = np.random.default_rng(8).normal(size=(n, n))
+    A0[:, 20] = np.nan
+    LU, ipiv, perm, _ = _factor(ctx, A0, torch.float64)
+    assert ((ipiv >= np.arange(n)) & (ipiv < n)).all()
+    np.testing.assert_array_equal(np.sort(perm.cpu().numpy()), np.arange(n))
+    assert bool(torch.isfinite(LU[:, :20]).all()) and bool(torch.isnan(LU[20, 20]))
