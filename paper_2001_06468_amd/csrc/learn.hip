@@ -303,14 +303,35 @@ __global__ __launch_bounds__(kThreads) void k_mlp_grad(
   }
 }
 
-// out[k] = sum over rows r (in order) of rows[r][k], k <= kCount
-__global__ void k_mlp_reduce(const float* __restrict__ rows, int32_t nrows,
-                             float* __restrict__ out) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k > kCount) return;
-  float s = 0.f;
-  for (int r = 0; r < nrows; ++r) s += rows[(int64_t)r * (kCount + 1) + k];
-  out[k] = s;
+// out[k] = sum over rows r of rows[r][k], k <= kCount: one workgroup per 64
+// entries, wave w takes rows w, w + 16, ... with four sums in flight, then the
+// waves' sums in order (the order of the sum depends on nrows alone).  Bound by
+// the latency of the loads: 256 rows (9.6 MB) 59.6 us with one thread per entry
+// walking all rows, 4.7 us so.
+constexpr int kRedWaves = 16;
+__global__ __launch_bounds__(64 * kRedWaves) void k_mlp_reduce(const float* __restrict__ rows,
+                                                               int32_t nrows,
+                                                               float* __restrict__ out) {
+  __shared__ float part[kRedWaves][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int k = blockIdx.x * 64 + lane;
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+  if (k <= kCount) {
+    const float* col = rows + k;
+    int r = w;
+    for (; r + 3 * kRedWaves < nrows; r += 4 * kRedWaves)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q] += col[(int64_t)(r + q * kRedWaves) * (kCount + 1)];
+    for (; r < nrows; r += kRedWaves) s[0] += col[(int64_t)r * (kCount + 1)];
+  }
+  part[w][lane] = (s[0] + s[1]) + (s[2] + s[3]);
+  __syncthreads();
+  if (w == 0 && k <= kCount) {
+    float t = 0.f;
+#pragma unroll
+    for (int q = 0; q < kRedWaves; ++q) t += part[q][lane];
+    out[k] = t;
+  }
 }
 
 __global__ void k_adam(int64_t count, float* __restrict__ th, const float* __restrict__ g,
@@ -474,8 +495,8 @@ hipError_t launch_mlp_grad(const float* th, int32_t nbodies, int64_t npts,
   if (nsel <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)nsel), dim3(kThreads), 0, s, th, nbodies, npts,
                      body_off, sel, nsel, phi, t_pt, t_body, rows, err);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(blocks_for(kCount + 1, 256)), dim3(256), 0, s, rows, nsel,
-                     grad);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3(blocks_for(kCount + 1, 64)), dim3(64 * kRedWaves), 0, s,
+                     rows, nsel, grad);
   return hipGetLastError();
 }
 
