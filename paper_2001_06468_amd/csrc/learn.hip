@@ -1,8 +1,16 @@
 // Learned warm start: a per-point network with pooled body context that
 // predicts, in each free body's own frame, the force density at its force
-// points and the body's (U, Omega).  One workgroup handles one body: its
-// points' features and hidden states live in LDS, lane j of every wave owns
-// hidden unit j (H = 64 = one wavefront), waves take points round-robin.
+// points and the body's (U, Omega).  One workgroup of 16 waves handles one body:
+// its points' features and hidden states live in LDS.  The three products with
+// 64 x 64 matrices (second layer, its weight gradient, the gradient passed back
+// through it) run on the matrix cores in 16 x 16 tiles of (points or units) x
+// units; elsewhere lane j of every wave owns hidden unit j (H = 64 = one
+// wavefront) and waves take points round-robin.  Hidden-state rows are 68
+// floats apart, so that the tiles' operand reads touch every bank.
+//
+// What bounds it: latency (one body is 1 Mflop; 256 bodies fill the chip once).
+// The gradient of 256 bodies of 40 points takes 19.5 us; 42.9 us when four waves
+// per body formed the products element by element.
 //
 //   h1_m = tanh(W1 phi_m + b1),          c = mean_m h1_m
 //   h2_m = tanh(W2 h1_m + V2 c + b2),    d = mean_m h2_m
@@ -23,8 +31,10 @@ constexpr int kH = kMlpHidden;    // hidden width (one wavefront)
 constexpr int kF = 7;             // input features
 constexpr int kO = 3;             // point outputs
 constexpr int kP = 6;             // body outputs
-constexpr int kThreads = 256;
+constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
+constexpr int kHS = kH + 4;       // row stride of the hidden states
+static_assert(kWaves == 16 && kH == 64, "tile and lane maps below");
 
 // offsets of the parameter groups in the flat vector
 constexpr int oW1 = 0;
@@ -39,25 +49,72 @@ constexpr int ob4 = oW4 + kP * kH;
 constexpr int kCount = ob4 + kP;
 static_assert(kCount == kMlpParams, "parameter layout");
 
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+template <int ctrl, int rows>
+__device__ inline float dpp(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, rows, 0xF, false));
 }
+// sum over each row of 16 lanes, in all of them
+__device__ inline float row_sum(float v) {
+  v += dpp<0xB1, 0xF>(v);    // quad [1,0,3,2]
+  v += dpp<0x4E, 0xF>(v);    // quad [2,3,0,1]
+  v += dpp<0x141, 0xF>(v);   // row_half_mirror
+  return v + dpp<0x140, 0xF>(v);   // row_mirror
+}
+// sum over the wave, the same value in every lane
+__device__ inline float wave_sum(float v) {
+  v = row_sum(v);
+  v += dpp<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+  v += dpp<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 struct MlpShared {
   float phi[kMlpMaxPts][8];
-  float h1[kMlpMaxPts][kH];
-  float h2[kMlpMaxPts][kH];
+  float h1[kMlpMaxPts][kHS];
+  float h2[kMlpMaxPts][kHS];
   float y[kMlpMaxPts][4];      // outputs, then their gradients
-  float c[kH], d[kH], vc[kH], sa2[kH], vs2[kH];
+  float c[kH], d[kH], vc[kH], sa2[kH], bz[kH];
   float part[kWaves][kH];
   float z[8], dz[8];
   float red[kWaves];
 };
+static_assert(sizeof(MlpShared) <= 160 * 1024, "one body per CU");
+
+// 16 x 16 tile of X W^T (T = false: out[p][j] = sum_i x[p][i] W[j][i]) or X W
+// (T = true: out[p][i] = sum_j x[p][j] W[j][i]), W 64 x 64 row-major: lane l
+// holds rows 4 (l / 16) + r of the tile (points), column l % 16 (units).  The
+// order of the 64 terms is the same permutation on both operands: step 4q + e of
+// lane group g takes term 16 q + 4 g + e, so that X is read as 16-byte vectors.
+template <bool T>
+__device__ inline floatx4 tile_times(const float (*x)[kHS], const float* __restrict__ W, int pt,
+                                     int jt, int lane) {
+  const int l = lane & 15, g = lane >> 4;
+  const float* xr = x[16 * pt + l] + 4 * g;
+  float b[16];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int k = 16 * q + 4 * g + e;
+      b[4 * q + e] = T ? W[k * kH + 16 * jt + l] : W[(16 * jt + l) * kH + k];
+    }
+  }
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const floatx4 a = *reinterpret_cast<const floatx4*>(xr + 16 * q);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[4 * q + e], acc, 0, 0, 0);
+  }
+  return acc;
+}
 
 // Forward pass of one body (points p0 .. p0+n-1 of phi).  Leaves h1, h2, c,
-// d, y and z in LDS.
+// d, y and z in LDS, and zero rows of h1 and h2 up to the next multiple of four.
 __device__ void body_forward(MlpShared& S, const float* __restrict__ th,
                              const float* __restrict__ phi, int64_t p0, int n) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -65,11 +122,15 @@ __device__ void body_forward(MlpShared& S, const float* __restrict__ th,
     const int p = e / kF, f = e - p * kF;
     S.phi[p][f] = phi[(p0 + p) * kF + f];
   }
-  __syncthreads();
   float w1[kF];
 #pragma unroll
   for (int f = 0; f < kF; ++f) w1[f] = th[oW1 + lane * kF + f];
   const float b1 = th[ob1 + lane];
+  // V2's entries of (unit tid / 16, four terms), for V2 c below
+  float v2[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v2[e] = th[oV2 + 4 * tid + e];
+  __syncthreads();
   float acc = 0.f;
   for (int p = w; p < n; p += kWaves) {
     float a = b1;
@@ -80,6 +141,7 @@ __device__ void body_forward(MlpShared& S, const float* __restrict__ th,
     acc += h;
   }
   S.part[w][lane] = acc;
+  if (n + w < ((n + 3) & ~3)) S.h1[n + w][lane] = S.h2[n + w][lane] = 0.f;
   __syncthreads();
   if (w == 0) {
     float s = 0.f;
@@ -88,28 +150,38 @@ __device__ void body_forward(MlpShared& S, const float* __restrict__ th,
     S.c[lane] = s / (float)n;
   }
   __syncthreads();
-  // V2 c + b2, then the second layer with W2's row `lane` in registers
-  if (w == 0) {
-    float a = th[ob2 + lane];
-    for (int i = 0; i < kH; ++i) a = fmaf(th[oV2 + lane * kH + i], S.c[i], a);
-    S.vc[lane] = a;
-  }
-  float w2[kH];
+  // V2 c + b2
+  {
+    const int j = tid >> 4, i = 4 * (tid & 15);
+    float a = 0.f;
 #pragma unroll
-  for (int i = 0; i < kH; ++i) w2[i] = th[oW2 + lane * kH + i];
+    for (int e = 0; e < 4; ++e) a = fmaf(v2[e], S.c[i + e], a);
+    a = row_sum(a);
+    if ((tid & 15) == 0) S.vc[j] = a + th[ob2 + j];
+  }
+  const int nt = (n + 15) / 16;   // tiles of points
   __syncthreads();
-  const float vcl = S.vc[lane];
-  acc = 0.f;
-  for (int p = w; p < n; p += kWaves) {
-    float a = vcl;
+  // second layer
+  for (int t = w; t < 4 * nt; t += kWaves) {
+    const int pt = t >> 2, jt = t & 3, j = 16 * jt + (lane & 15);
+    const floatx4 v = tile_times<false>(S.h1, th + oW2, pt, jt, lane);
+    const float vcl = S.vc[j];
+    float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < kH; ++i) a = fmaf(w2[i], S.h1[p][i], a);
-    const float h = tanhf(a);
-    S.h2[p][lane] = h;
-    acc += h;
+    for (int r = 0; r < 4; ++r) {
+      const int p = 16 * pt + 4 * (lane >> 4) + r;
+      if (p < n) {
+        const float h = tanhf(v[r] + vcl);
+        S.h2[p][j] = h;
+        sum += h;
+      }
+    }
+    sum += __shfl_xor(sum, 16);
+    sum += __shfl_xor(sum, 32);
+    if (lane < 16) S.part[pt][j] = sum;
   }
-  S.part[w][lane] = acc;
   const float w30 = th[oW3 + lane], w31 = th[oW3 + kH + lane], w32 = th[oW3 + 2 * kH + lane];
+  __syncthreads();
   for (int p = w; p < n; p += kWaves) {
     const float h = S.h2[p][lane];
     const float y0 = wave_sum(w30 * h), y1 = wave_sum(w31 * h), y2 = wave_sum(w32 * h);
@@ -119,18 +191,13 @@ __device__ void body_forward(MlpShared& S, const float* __restrict__ th,
       S.y[p][2] = y2 + th[ob3 + 2];
     }
   }
-  __syncthreads();
-  if (w == 0) {
+  if (w < kP) {   // wave o forms body output o; wave 0 also leaves d
     float s = 0.f;
-#pragma unroll
-    for (int q = 0; q < kWaves; ++q) s += S.part[q][lane];
+    for (int q = 0; q < nt; ++q) s += S.part[q][lane];
     const float dl = s / (float)n;
-    S.d[lane] = dl;
-#pragma unroll
-    for (int o = 0; o < kP; ++o) {
-      const float v = wave_sum(th[oW4 + o * kH + lane] * dl);
-      if (lane == 0) S.z[o] = v + th[ob4 + o];
-    }
+    if (w == 0) S.d[lane] = dl;
+    const float v = wave_sum(th[oW4 + w * kH + lane] * dl);
+    if (lane == 0) S.z[w] = v + th[ob4 + w];
   }
   __syncthreads();
 }
@@ -208,97 +275,116 @@ __global__ __launch_bounds__(kThreads) void k_mlp_grad(
   zs = wave_sum(zs) / (float)kP;
   if (lane == 0) S.red[w] = lsum + (w == 0 ? zs : 0.f);
   __syncthreads();
-  if (tid == 0) g[kCount] = (S.red[0] + S.red[1] + S.red[2] + S.red[3]) * invM;
+  if (tid == 0) {
+    float s = 0.f;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) s += S.red[q];
+    g[kCount] = s * invM;
+  }
   // dW4, db4 (outer products with d)
   for (int e = tid; e < kP * kH; e += kThreads) g[oW4 + e] = S.dz[e / kH] * S.d[e % kH];
   if (tid < kP) g[ob4 + tid] = S.dz[tid];
-  // dW3, db3; then da2 = (W3^T dy + W4^T dz / n) (1 - h2^2) in place of h2
-  {
-    float a0 = 0.f, a1 = 0.f, a2 = 0.f;
-    const float w30 = th[oW3 + lane], w31 = th[oW3 + kH + lane], w32 = th[oW3 + 2 * kH + lane];
-    float bz = 0.f;
+  // dW3, db3, and W4^T dz / n
+  if (w < kO) {
+    float s = 0.f;
+    for (int p = 0; p < n; ++p) s = fmaf(S.y[p][w], S.h2[p][lane], s);
+    g[oW3 + w * kH + lane] = s;
+  } else if (w == kO) {
+    float s = 0.f;
 #pragma unroll
-    for (int o = 0; o < kP; ++o) bz = fmaf(th[oW4 + o * kH + lane], S.dz[o], bz);
-    bz /= (float)n;
+    for (int o = 0; o < kP; ++o) s = fmaf(th[oW4 + o * kH + lane], S.dz[o], s);
+    S.bz[lane] = s / (float)n;
+  } else if (w < 4 + kO) {
+    const int o = w - 4;
+    float s = 0.f;
+    for (int p = lane; p < n; p += 64) s += S.y[p][o];
+    s = wave_sum(s);
+    if (lane == 0) g[ob3 + o] = s;
+  }
+  const float w30 = th[oW3 + lane], w31 = th[oW3 + kH + lane], w32 = th[oW3 + 2 * kH + lane];
+  __syncthreads();
+  // da2 = (W3^T dy + W4^T dz / n) (1 - h2^2) in place of h2
+  {
+    const float bz = S.bz[lane];
     float s2 = 0.f;
     for (int p = w; p < n; p += kWaves) {
       const float h = S.h2[p][lane];
       const float d0 = S.y[p][0], d1 = S.y[p][1], d2 = S.y[p][2];
-      a0 = fmaf(d0, h, a0);
-      a1 = fmaf(d1, h, a1);
-      a2 = fmaf(d2, h, a2);
       const float dh = fmaf(w30, d0, fmaf(w31, d1, fmaf(w32, d2, bz)));
       const float da = dh * (1.f - h * h);
       S.h2[p][lane] = da;
       s2 += da;
     }
-    // fixed-order cross-wave sums through LDS
-    __shared__ float cw[kWaves][4][kH];
-    cw[w][0][lane] = a0;
-    cw[w][1][lane] = a1;
-    cw[w][2][lane] = a2;
-    cw[w][3][lane] = s2;
-    __syncthreads();
-    if (w == 0) {
-      float r0 = 0.f, r1 = 0.f, r2 = 0.f, r3 = 0.f;
-#pragma unroll
-      for (int q = 0; q < kWaves; ++q) {
-        r0 += cw[q][0][lane];
-        r1 += cw[q][1][lane];
-        r2 += cw[q][2][lane];
-        r3 += cw[q][3][lane];
-      }
-      g[oW3 + lane] = r0;
-      g[oW3 + kH + lane] = r1;
-      g[oW3 + 2 * kH + lane] = r2;
-      S.sa2[lane] = r3;
-      g[ob2 + lane] = r3;
-    }
-    __syncthreads();
+    S.part[w][lane] = s2;
   }
-  if (tid < kO) {
-    float s = 0.f;
-    for (int p = 0; p < n; ++p) s += S.y[p][tid];
-    g[ob3 + tid] = s;
-  }
-  // dW2[j][i] = sum_p da2[p][j] h1[p][i];  dV2[j][i] = sa2[j] c[i]
-  for (int e = tid; e < kH * kH; e += kThreads) {
-    const int j = e / kH, i = e - j * kH;
-    float s = 0.f;
-    for (int p = 0; p < n; ++p) s = fmaf(S.h2[p][j], S.h1[p][i], s);
-    g[oW2 + e] = s;
-    g[oV2 + e] = S.sa2[j] * S.c[i];
-  }
-  // V2^T sa2 / n (lane = i)
+  __syncthreads();
   if (w == 0) {
     float s = 0.f;
-    for (int j = 0; j < kH; ++j) s = fmaf(th[oV2 + j * kH + lane], S.sa2[j], s);
-    S.vs2[lane] = s / (float)n;
-  }
-  float w2c[kH];
 #pragma unroll
-  for (int j = 0; j < kH; ++j) w2c[j] = th[oW2 + j * kH + lane];
+    for (int q = 0; q < kWaves; ++q) s += S.part[q][lane];
+    S.sa2[lane] = s;
+    g[ob2 + lane] = s;
+  }
+  // dW2[j][i] = sum_p da2[p][j] h1[p][i]: wave w the tile (w / 4, w % 4)
+  {
+    const int j0 = 16 * (w >> 2), i0 = 16 * (w & 3), l = lane & 15, gq = lane >> 4;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int p = gq; p < ((n + 3) & ~3); p += 4)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(S.h2[p][j0 + l], S.h1[p][i0 + l], acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) g[oW2 + (j0 + 4 * gq + r) * kH + i0 + l] = acc[r];
+  }
+  __syncthreads();
+  // dV2[j][i] = sa2[j] c[i];  V2^T sa2 / n (lane = i), four units per wave
+  {
+    float s = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int j = 4 * w + q;
+      const float sj = S.sa2[j];
+      g[oV2 + j * kH + lane] = sj * S.c[lane];
+      s = fmaf(th[oV2 + j * kH + lane], sj, s);
+    }
+    S.part[w][lane] = s;
+  }
+  __syncthreads();
+  if (w == 0) {
+    float s = 0.f;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) s += S.part[q][lane];
+    S.vc[lane] = s / (float)n;
+  }
   __syncthreads();
   // da1 = (W2^T da2 + V2^T sa2 / n) (1 - h1^2) in place of h1
-  const float vs = S.vs2[lane];
-  for (int p = w; p < n; p += kWaves) {
-    float a = vs;
+  for (int t = w; t < 4 * ((n + 15) / 16); t += kWaves) {
+    const int pt = t >> 2, it = t & 3, i = 16 * it + (lane & 15);
+    const floatx4 v = tile_times<true>(S.h2, th + oW2, pt, it, lane);
+    const float vs = S.vc[i];
 #pragma unroll
-    for (int j = 0; j < kH; ++j) a = fmaf(w2c[j], S.h2[p][j], a);
-    const float h = S.h1[p][lane];
-    S.h1[p][lane] = a * (1.f - h * h);
+    for (int r = 0; r < 4; ++r) {
+      const int p = 16 * pt + 4 * (lane >> 4) + r;
+      if (p < n) {
+        const float h = S.h1[p][i];
+        S.h1[p][i] = (v[r] + vs) * (1.f - h * h);
+      }
+    }
   }
   __syncthreads();
-  // dW1[i][f] = sum_p da1[p][i] phi[p][f];  db1[i] = sum_p da1[p][i]
-  for (int e = tid; e < kH * (kF + 1); e += kThreads) {
-    const int i = e / (kF + 1), f = e - i * (kF + 1);
+  // dW1[i][f] = sum_p da1[p][i] phi[p][f];  db1[i] = sum_p da1[p][i] (f = kF):
+  // one thread per (f, i) of half of the points, then both halves
+  {
+    const int i = tid & 63, f = (tid >> 6) & 7, half = tid >> 9;
     float s = 0.f;
-    if (f < kF) {
-      for (int p = 0; p < n; ++p) s = fmaf(S.h1[p][i], S.phi[p][f], s);
-      g[oW1 + i * kF + f] = s;
-    } else {
-      for (int p = 0; p < n; ++p) s += S.h1[p][i];
-      g[ob1 + i] = s;
+    if (f < kF)
+      for (int p = half; p < n; p += 2) s = fmaf(S.h1[p][i], S.phi[p][f], s);
+    else
+      for (int p = half; p < n; p += 2) s += S.h1[p][i];
+    S.part[w][lane] = s;
+    __syncthreads();
+    if (half == 0) {
+      const float v = S.part[w][lane] + S.part[w + 8][lane];
+      if (f < kF) g[oW1 + i * kF + f] = v;
+      else g[ob1 + i] = v;
     }
   }
 }
