@@ -12,7 +12,7 @@
 //             panel are resolved in registers) and, right of the panel, solves
 //             with the unit lower jb x jb block (the U12 row block);
 //   update  : A22 -= L21 U12 on the matrix cores (16x16x4 MFMA, FP32 or FP64),
-//             128 x 128 output tile per workgroup.
+//             64 x 64 output tile per workgroup.
 // The composite row permutation is carried along as an extra column so that
 // solves can gather the right-hand side in one pass.
 #include <algorithm>
@@ -396,9 +396,8 @@ struct Mfma<double> {
   static __device__ inline int row(int lane, int r) { return (lane >> 4) + 4 * r; }
 };
 
-constexpr int kGT = 128;       // output tile edge per workgroup
+constexpr int kGT = 64;        // output tile edge per workgroup
 constexpr int kGK = 64;        // the panel width: every update is rank 64 (K <= kGK)
-constexpr int kGES = kGT + 2;  // column stride of the epilogue tile
 
 // LDS of one update tile: the A panel [kGK][kGT] and the B panel [kGT][kGK]
 // (k contiguous per column) in 16-byte chunks of E elements, XOR-swizzled so
@@ -408,6 +407,7 @@ constexpr int kGES = kGT + 2;  // column stride of the epilogue tile
 // then the output tile [col][row] (stride kGES) for the coalesced epilogue.
 template <class T>
 struct GemmLds {
+  static constexpr int kGES = kGT + 2;  // column stride of the epilogue tile
   static constexpr int E = 16 / (int)sizeof(T);
   static constexpr int kSize =
       2 * kGK * kGT > kGT * kGES ? 2 * kGK * kGT : kGT * kGES;
@@ -446,14 +446,19 @@ __device__ inline void gemm_panels_lds(T* S, const T* __restrict__ Ap, const T* 
 }
 
 // C (m x nc) -= A (m x K) * B (K x nc); all column-major with leading dim lda,
-// K <= kGK.  256 threads = 2 x 2 waves, each wave a 64 x 64 sub-tile of 4 x 4
-// MFMA blocks.  MFMA 16x16x4 operand layout: lane l holds A[l%16][l/16] and
+// K <= kGK.  256 threads = 2 x 2 waves, each wave a quarter of the kGT x kGT tile
+// in MFMA blocks of 16 x 16.  MFMA 16x16x4 operand layout: lane l holds A[l%16][l/16] and
 // B[l/16][l%16]; the output row of register r is Mfma<T>::row(l, r), the
 // column l%16.  Interior tiles of a full panel (dma != 0: 16-byte aligned
 // panels) load both panels with 16-byte global-to-LDS loads; edge tiles load
 // element by element with zeros outside.  The products run over k up to K
 // rounded up to 32, in increasing k, and C is updated through LDS one column
 // per 64 lanes.
+// A tile is mostly latency (panels in, 64 matrix-core steps, C in and out: 11 to
+// 15 us alone), so small tiles, two workgroups per CU, win at every order tried
+// over 128 x 128 tiles that fill a CU's LDS: FP64 rank-64 updates of n = 3150 54.1 ->
+// 30.3 us on average (66.5 us, 2.3 TB/s of C, at full size), of
+// n = 630 39.3 -> 15.6 us, factorisation of n = 8000 56.5 -> 48.9 ms.
 template <class T>
 __global__ __launch_bounds__(256) void k_gemm_update(int64_t m, int64_t nc, int K,
                                                      const T* __restrict__ Ap,
@@ -465,7 +470,8 @@ __global__ __launch_bounds__(256) void k_gemm_update(int64_t m, int64_t nc, int 
   typedef typename Mfma<T>::acc_t acc_t;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int64_t i0 = blockIdx.x * (int64_t)kGT, j0 = blockIdx.y * (int64_t)kGT;
-  const int wr = (wid >> 1) * 64, wc = (wid & 1) * 64;
+  constexpr int kGES = G::kGES, NB = kGT / 32;
+  const int wr = (wid >> 1) * (kGT / 2), wc = (wid & 1) * (kGT / 2);
   if (dma && K == kGK && i0 + kGT <= m && j0 + kGT <= nc) {
     gemm_panels_lds<T>(S, Ap, Bp, lda, i0, j0, wid, lane);
   } else {
@@ -481,32 +487,32 @@ __global__ __launch_bounds__(256) void k_gemm_update(int64_t m, int64_t nc, int 
     }
   }
   __syncthreads();
-  acc_t acc[4][4];
+  acc_t acc[NB][NB];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < NB; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[a][b][r] = T(0);
   const int kend = ((K + 31) / 32) * 32;
   const int li = lane & 15;
   for (int kk = 0; kk < kend; kk += 4) {
     const int kr = kk + (lane >> 4);
-    T av[4], bv[4];
+    T av[NB], bv[NB];
 #pragma unroll
-    for (int a = 0; a < 4; ++a) av[a] = S[G::a_at(kr, wr + a * 16 + li)];
+    for (int a = 0; a < NB; ++a) av[a] = S[G::a_at(kr, wr + a * 16 + li)];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) bv[b] = S[G::b_at(kr, wc + b * 16 + li)];
+    for (int b = 0; b < NB; ++b) bv[b] = S[G::b_at(kr, wc + b * 16 + li)];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < NB; ++a)
 #pragma unroll
-      for (int b = 0; b < 4; ++b) acc[a][b] = Mfma<T>::run(av[a], bv[b], acc[a][b]);
+      for (int b = 0; b < NB; ++b) acc[a][b] = Mfma<T>::run(av[a], bv[b], acc[a][b]);
   }
   __syncthreads();  // every operand read is done: the tile becomes the output
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < NB; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         S[(wc + b * 16 + li) * kGES + wr + a * 16 + Mfma<T>::row(lane, r)] = acc[a][b][r];
@@ -1109,13 +1115,14 @@ hipError_t launch_lu_factor(int64_t n, T* A, int64_t lda, int32_t* ipiv, int32_t
                        jb, 0, A, lda, ipiv, perm);
     const int64_t rest = n - k - jb;
     if (rest > 0) {
-      dim3 g((unsigned)((rest + kGT - 1) / kGT), (unsigned)((rest + kGT - 1) / kGT));
       // global-to-LDS panel loads need 16-byte aligned panels
       const int E = 16 / (int)sizeof(T);
       const int dma = ((uintptr_t)A % 16 == 0 && lda % E == 0 && (k + jb) % E == 0 && k % E == 0);
-      hipLaunchKernelGGL(k_gemm_update<T>, g, dim3(256), 0, s, rest, rest, jb,
-                         A + (k + jb) + k * lda, A + k + (k + jb) * lda,
-                         A + (k + jb) + (k + jb) * lda, lda, dma);
+      const T *Ap = A + (k + jb) + k * lda, *Bp = A + k + (k + jb) * lda;
+      T* C = A + (k + jb) + (k + jb) * lda;
+      const unsigned t = (unsigned)((rest + kGT - 1) / kGT);
+      hipLaunchKernelGGL(k_gemm_update<T>, dim3(t, t), dim3(256), 0, s, rest, rest, jb, Ap, Bp, C,
+                         lda, dma);
     }
   }
   return hipGetLastError();
