@@ -107,3 +107,13 @@ def test_panel_nan_column_stays_in_range(ctx):
     assert ((ipiv >= np.arange(n)) & (ipiv < n)).all()
     np.testing.assert_array_equal(np.sort(perm.cpu().numpy()), np.arange(n))
     assert bool(torch.isfinite(LU[:, :20]).all()) and bool(torch.isnan(LU[20, 20]))
+
+
+def test_rows_above_an_infinity_stay_finite(ctx):
+    """An infinite entry in a U row does not reach the rows above it (0 * inf)."""
+    n = 130
+    A0 = np.random.default_rng(9).normal(size=(n, n)) + 4 * n * np.eye(n)
+    A0[30, 100] = np.inf
+    LU, ipiv, _, _ = _factor(ctx, A0, torch.float64)
+    np.testing.assert_array_equal(ipiv[:64], np.arange(64))
+    assert bool(torch.isfinite(LU[:30, :]).all()) and bool(torch.isinf(LU[30, 100]))
