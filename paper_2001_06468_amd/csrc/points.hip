@@ -1,5 +1,7 @@
 // Geometry at time t, nearest-neighbour map and the nu-sorted (CSR) layout of
 // the quadrature points.
+#include <type_traits>
+
 #include "nrs_internal.h"
 
 namespace nrs {
@@ -112,70 +114,107 @@ __global__ void k_geometry(GeomSet g0, GeomSet g1, int64_t nb0, int32_t M, int32
   geometry_point(g, i, M, P, wave, Y, t);
 }
 
-// One thread per quadrature point; force points of the block's groups are
-// staged through LDS.  Squared distance without contraction so that the
-// result equals the (dx*dx + dy*dy) + dz*dz of a plain FP64 evaluation.
+// kNnSplit consecutive lanes per quadrature point, each over every kNnSplit-th
+// force point of the point's group, in increasing order, then the smallest
+// (distance, index) of them.  Squared distance without contraction so that the
+// result equals the (dx*dx + dy*dy) + dz*dz of a plain FP64 evaluation; the first
+// force point stands until one is strictly nearer (also where its distance is
+// not a number).
+// What bounds it: one lane's chain of dependent FP64 operations when a group is
+// small (a filament's 40 points), FP64 issue when it is large.  With one thread per
+// quadrature point over force points in LDS, 10,000 points in groups of 40
+// took NN_A0 us (40 workgroups, NN_A1 us so), 32,000 points in one group of 2000
+// NN_B0 us (NN_B1 us so).
 constexpr int kNnBlock = 256;
+constexpr int kNnSplit = 8;
+// kPer points per lane group share the loads of a force point; one point where
+// more would leave SIMDs without a wave (kNnManyQ).
+constexpr int64_t kNnManyQ = 32768;
+template <int kPer>
 __global__ __launch_bounds__(kNnBlock) void k_nearest(int64_t N, const double* __restrict__ x,
                                                       GroupTable gt, int64_t Q,
                                                       const double* __restrict__ X,
                                                       const int32_t* __restrict__ groupX,
                                                       int32_t* __restrict__ nu) {
 #pragma clang fp contract(off)
-  __shared__ double sx[kNnBlock], sy[kNnBlock], sz[kNnBlock];
-  __shared__ int s_lo, s_hi;
-  const int64_t q = blockIdx.x * (int64_t)kNnBlock + threadIdx.x;
-  const bool active = q < Q;
-  int lo = 0, hi = 0;
-  double qx = 0, qy = 0, qz = 0;
-  if (active) {
-    const int g = groupX[q];
-    if (g >= 0 && g < gt.G) {
-      lo = gt.off[g];
-      hi = gt.off[g + 1];
+  const int64_t q0 = (blockIdx.x * (int64_t)kNnBlock + threadIdx.x) / kNnSplit * kPer;
+  const int sub = threadIdx.x % kNnSplit;
+  int lo[kPer], hi[kPer], ulo = 0x7fffffff, uhi = 0;   // each point's group, all of them
+  double qx[kPer], qy[kPer], qz[kPer], best[kPer];
+  int arg[kPer];
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int64_t q = q0 + e;
+    lo[e] = hi[e] = 0;
+    qx[e] = qy[e] = qz[e] = 0.0;
+    best[e] = __builtin_huge_val();
+    arg[e] = 0x7fffffff;
+    if (q < Q) {
+      const int g = groupX[q];
+      if (g >= 0 && g < gt.G) {
+        lo[e] = gt.off[g];
+        hi[e] = gt.off[g + 1];
+      }
+      qx[e] = X[q];
+      qy[e] = X[Q + q];
+      qz[e] = X[2 * Q + q];
     }
-    qx = X[q];
-    qy = X[Q + q];
-    qz = X[2 * Q + q];
-  }
-  if (threadIdx.x == 0) {
-    s_lo = 0x7fffffff;
-    s_hi = -1;
-  }
-  __syncthreads();
-  if (active && hi > lo) {
-    atomicMin(&s_lo, lo);
-    atomicMax(&s_hi, hi);
-  }
-  __syncthreads();
-  const int blo = s_lo, bhi = s_hi;
-  double best = __builtin_huge_val();
-  int arg = -1;
-  for (int base = blo; base < bhi; base += kNnBlock) {
-    const int j = base + threadIdx.x;
-    if (j < bhi) {
-      sx[threadIdx.x] = x[j];
-      sy[threadIdx.x] = x[N + j];
-      sz[threadIdx.x] = x[2 * N + j];
+    if (hi[e] > lo[e]) {
+      ulo = min(ulo, lo[e]);
+      uhi = max(uhi, hi[e]);
     }
-    __syncthreads();
-    const int cnt = min(kNnBlock, bhi - base);
-    for (int c = 0; c < cnt; ++c) {
-      const int nidx = base + c;
-      if (nidx >= lo && nidx < hi) {
-        const double dx = sx[c] - qx;
-        const double dy = sy[c] - qy;
-        const double dz = sz[c] - qz;
+  }
+  if (uhi == 0) ulo = 0;   // no point of this lane group has candidates
+  // every lane starts from the first force point (not a number: nothing is nearer)
+  bool mixed = false;
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    mixed = mixed || lo[e] != ulo || hi[e] != uhi;
+    if (hi[e] > lo[e]) {
+      const int j = lo[e];
+      const double dx = x[j] - qx[e];
+      const double dy = x[N + j] - qy[e];
+      const double dz = x[2 * N + j] - qz[e];
+      const double d2 = dx * dx + dy * dy + dz * dz;
+      best[e] = d2 == d2 ? d2 : -1.0;
+      arg[e] = j;
+    }
+  }
+  auto scan = [&](auto all) {
+#pragma clang fp contract(off)
+#pragma unroll 4
+    for (int j = ulo + sub; j < uhi; j += kNnSplit) {
+      const double px = x[j], py = x[N + j], pz = x[2 * N + j];
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) {
+        const double dx = px - qx[e];
+        const double dy = py - qy[e];
+        const double dz = pz - qz[e];
         const double d2 = dx * dx + dy * dy + dz * dz;
-        if (d2 < best || arg < 0) {
-          best = d2;
-          arg = nidx;
+        if (d2 < best[e] && (decltype(all)::value || (j >= lo[e] && j < hi[e]))) {
+          best[e] = d2;
+          arg[e] = j;
         }
       }
     }
-    __syncthreads();
+  };
+  if (kPer == 1 || !__any(mixed))
+    scan(std::true_type{});   // each lane's points share one group
+  else
+    scan(std::false_type{});
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+#pragma unroll
+    for (int o = 1; o < kNnSplit; o <<= 1) {
+      const double ob = __shfl_xor(best[e], o, 64);
+      const int oa = __shfl_xor(arg[e], o, 64);
+      if (ob < best[e] || (ob == best[e] && oa < arg[e])) {
+        best[e] = ob;
+        arg[e] = oa;
+      }
+    }
+    if (q0 + e < Q && sub == 0) nu[q0 + e] = hi[e] > lo[e] ? arg[e] : -1;
   }
-  if (active) nu[q] = arg;
 }
 
 __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n) {
@@ -263,6 +302,7 @@ __global__ __launch_bounds__(kScanBlock) void k_csr_scan(int64_t N, int32_t* cnt
 // is arbitrary until k_csr_finish sorts it.
 constexpr int64_t kCsrSmallN = 8192;
 constexpr int64_t kCsrSmallQ = 1 << 17;
+constexpr int kCsrBatch = 8;
 __global__ __launch_bounds__(kScanBlock) void k_csr_small(int64_t N, int64_t Q,
                                                           const int32_t* __restrict__ nu,
                                                           int32_t* __restrict__ seg,
@@ -273,9 +313,17 @@ __global__ __launch_bounds__(kScanBlock) void k_csr_small(int64_t N, int64_t Q,
   const int tid = threadIdx.x;
   for (int64_t i = tid; i < N + 2; i += kScanBlock) c[i] = 0;
   __syncthreads();
-  for (int64_t q = tid; q < Q; q += kScanBlock) {
-    const int32_t v = nu[q];
-    atomicAdd(&c[(v >= 0 && v < N) ? v : N + 1], 1);
+  // kCsrBatch loads in flight per thread: one workgroup is bound by their latency
+  for (int64_t q = tid; q < Q; q += kCsrBatch * kScanBlock) {
+    int32_t v[kCsrBatch];
+#pragma unroll
+    for (int e = 0; e < kCsrBatch; ++e) {
+      const int64_t qe = q + e * kScanBlock;
+      v[e] = qe < Q ? nu[qe] : -2;
+    }
+#pragma unroll
+    for (int e = 0; e < kCsrBatch; ++e)
+      if (q + e * kScanBlock < Q) atomicAdd(&c[(v[e] >= 0 && v[e] < N) ? v[e] : N + 1], 1);
   }
   __syncthreads();
   if (tid == 0 && st && c[N + 1] > 0) {
@@ -297,9 +345,16 @@ __global__ __launch_bounds__(kScanBlock) void k_csr_small(int64_t N, int64_t Q,
   }
   if (tid == kScanBlock - 1) seg[N] = total;
   __syncthreads();
-  for (int64_t q = tid; q < Q; q += kScanBlock) {
-    const int32_t v = nu[q];
-    if (v >= 0 && v < N) perm[atomicAdd(&c[v], 1)] = (int32_t)q;
+  for (int64_t q = tid; q < Q; q += kCsrBatch * kScanBlock) {
+    int32_t v[kCsrBatch];
+#pragma unroll
+    for (int e = 0; e < kCsrBatch; ++e) {
+      const int64_t qe = q + e * kScanBlock;
+      v[e] = qe < Q ? nu[qe] : -1;
+    }
+#pragma unroll
+    for (int e = 0; e < kCsrBatch; ++e)
+      if (v[e] >= 0 && v[e] < N) perm[atomicAdd(&c[v[e]], 1)] = (int32_t)(q + e * kScanBlock);
   }
 }
 
@@ -412,8 +467,12 @@ hipError_t launch_geometry(const nrs_scene& sc, double t, const double* Y, doubl
 hipError_t launch_nearest(int64_t N, const double* x, const GroupTable& gt, int64_t Q,
                           const double* X, const int32_t* groupX, int32_t* nu, hipStream_t s) {
   if (Q == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_nearest, grid1(Q, kNnBlock), dim3(kNnBlock), 0, s, N, x, gt, Q, X, groupX,
-                     nu);
+  if (Q < kNnManyQ)
+    hipLaunchKernelGGL(k_nearest<1>, grid1(Q * kNnSplit, kNnBlock), dim3(kNnBlock), 0, s, N, x, gt,
+                       Q, X, groupX, nu);
+  else
+    hipLaunchKernelGGL(k_nearest<4>, grid1((Q + 3) / 4 * kNnSplit, kNnBlock), dim3(kNnBlock), 0, s,
+                       N, x, gt, Q, X, groupX, nu);
   return hipGetLastError();
 }
 
