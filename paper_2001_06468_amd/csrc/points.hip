@@ -123,8 +123,9 @@ __global__ void k_geometry(GeomSet g0, GeomSet g1, int64_t nb0, int32_t M, int32
 // What bounds it: one lane's chain of dependent FP64 operations when a group is
 // small (a filament's 40 points), FP64 issue when it is large.  With one thread per
 // quadrature point over force points in LDS, 10,000 points in groups of 40
-// took NN_A0 us (40 workgroups, NN_A1 us so), 32,000 points in one group of 2000
-// NN_B0 us (NN_B1 us so).
+// took 14.5 us (40 workgroups; 4.4 us so), 32,000 points in one group of 2000
+// 207 us (98 us so), 74,000 in one of 4624 537 us (227 us so; 382 us while every
+// lane tested every point's own range).
 constexpr int kNnBlock = 256;
 constexpr int kNnSplit = 8;
 // kPer points per lane group share the loads of a force point; one point where
@@ -302,6 +303,10 @@ __global__ __launch_bounds__(kScanBlock) void k_csr_scan(int64_t N, int32_t* cnt
 // is arbitrary until k_csr_finish sorts it.
 constexpr int64_t kCsrSmallN = 8192;
 constexpr int64_t kCsrSmallQ = 1 << 17;
+// loads in flight per thread (the one workgroup is bound by their latency): 32,000
+// points 21 -> 11.7 us.  Measured slower: one atomic per run of equal nu, found
+// by lane shuffles (10.7 against 8.2 us at 10,000 points) or by consecutive points per
+// thread (68 against 25 us at 40,000).
 constexpr int kCsrBatch = 8;
 __global__ __launch_bounds__(kScanBlock) void k_csr_small(int64_t N, int64_t Q,
                                                           const int32_t* __restrict__ nu,
@@ -313,7 +318,6 @@ __global__ __launch_bounds__(kScanBlock) void k_csr_small(int64_t N, int64_t Q,
   const int tid = threadIdx.x;
   for (int64_t i = tid; i < N + 2; i += kScanBlock) c[i] = 0;
   __syncthreads();
-  // kCsrBatch loads in flight per thread: one workgroup is bound by their latency
   for (int64_t q = tid; q < Q; q += kCsrBatch * kScanBlock) {
     int32_t v[kCsrBatch];
 #pragma unroll
