@@ -30,9 +30,8 @@ nrs_status use_device(nrs_ctx* ctx) {
   return NRS_OK;
 }
 
-// chunk partial sums the matrix-free product may need: it runs the field
-// pair sum at the N force points
-int32_t apply_chunks(int64_t N, int64_t Q) { return field_plan(N, Q).cap; }
+// chunk partial sums the matrix-free product may need
+int32_t apply_chunks(int64_t N, int64_t Q) { return apply_plan(N, Q).cap; }
 
 bool uses_fp32(int32_t method) {
   return method == NRS_FP32_IR || method == NRS_FP32_GEPP_IR || method == NRS_FP32_GMRES_IR ||
@@ -138,7 +137,6 @@ bool carve_solve(Arena& ar, int64_t N, int64_t Q, int32_t M, int32_t method, Sol
   sb.srt.X32hi = ar.take<float4>(Q);
   sb.srt.X32lo = ar.take<float4>(Q);
   sb.srt.W = ar.take<double>(N);
-  sb.srt.fsrc = ar.take<FieldSrc>(Q);
   sb.lda = lda_for(n);
   sb.A32 = uses_fp32(method) ? ar.take<float>((size_t)sb.lda * n) : nullptr;
   sb.A64 = with64 ? ar.take<double>((size_t)sb.lda * n) : nullptr;

@@ -9,6 +9,8 @@
 // segment with wave-uniform (scalar) loads and sums the segment in registers:
 // the segmented reduction over nu needs no cross-lane traffic and the dense
 // 3N x 3Q stokeslet matrix is never formed.
+#include <algorithm>
+
 #include "nrs_internal.h"
 
 namespace nrs {
@@ -234,6 +236,104 @@ __global__ void k_rhs(int64_t N, int32_t M, const double* __restrict__ u,
   if (b32) b32[i] = (float)v;
 }
 
+// Pair sum of the matrix-free product: chunk partial sums of the flow of the
+// force densities f at the N force points (one per lane).  The sources are the
+// nu-sorted quadrature points, so a wave reads a 32-byte record (position and
+// weight) per pair by scalar load and a force density once per segment, and no
+// pass gathers sources first.  Workgroups are dealt to the eight XCDs in turn; with
+// at least eight chunks, workgroup 8 (pb + pblocks k) + x takes block pb of 64
+// points and chunk 8k + x, so an XCD's L2 holds its eighth of the sources.  Wave w
+// sums a contiguous quarter of its chunk, the four wave sums are added in a fixed
+// order.
+// What bounds it: FP64 issue (26 instructions and a quarter-rate reciprocal square
+// root per pair), and below about 10^7 pairs the launch and the scalar loads' latency,
+// hence the short chunks of apply_plan().  Against gathering 64-byte source records
+// first and the tracers' chunks of 256 sources (mean over calls, converged ones
+// that exit included): one filament (40 x 400 pairs) 16.5 -> 5.9 us, 25 filaments
+// (1000 x 10,000) 21.6 -> 14.3 us, 100 filaments (4000 x 40,000) 100.8 -> 102.9 us.
+constexpr int kPairThreads = 256;
+constexpr int kPairWaves = kPairThreads / 64;
+__global__ __launch_bounds__(kPairThreads) void k_apply_pairs(
+    int64_t N, int64_t pblocks, int32_t chunks, int64_t chunk, const double* __restrict__ x,
+    const int32_t* __restrict__ seg, const int32_t* __restrict__ nus,
+    const double4* __restrict__ X64, const double* __restrict__ f, double eps2,
+    double* __restrict__ part, const int32_t* __restrict__ stop) {
+  if (stop && *stop) return;
+  __shared__ double red[3][kPairWaves][64];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int32_t ch;
+  int64_t pb;
+  if (chunks >= 8) {
+    const int64_t j = blockIdx.x >> 3;
+    pb = j % pblocks;
+    ch = 8 * (int32_t)(j / pblocks) + (int32_t)(blockIdx.x & 7);
+    if (ch >= chunks) return;
+  } else {
+    ch = blockIdx.x % chunks;
+    pb = blockIdx.x / chunks;
+  }
+  const int64_t m = pb * 64 + lane;
+  double px = 0.0, py = 0.0, pz = 0.0;
+  if (m < N) {
+    px = x[m];
+    py = x[N + m];
+    pz = x[2 * N + m];
+  }
+  // this wave's sorted sources [a, b), wave-uniform (points outside every segment
+  // are not in the layout: seg[N] of them at most Q)
+  const int64_t total = seg[N];
+  const int64_t q0 = min<int64_t>(total, (int64_t)ch * chunk);
+  const int64_t q1 = min<int64_t>(total, q0 + chunk);
+  const int64_t per = (q1 - q0 + kPairWaves - 1) / kPairWaves;
+  const int64_t a64 = min<int64_t>(q1, q0 + w * per);
+  const int b = __builtin_amdgcn_readfirstlane((int)min<int64_t>(q1, a64 + per));
+  int p = __builtin_amdgcn_readfirstlane((int)a64);
+  double ux = 0.0, uy = 0.0, uz = 0.0;
+  if (p < b) {
+    int n = __builtin_amdgcn_readfirstlane(nus[p]);
+    double gx = f[n], gy = f[N + n], gz = f[2 * N + n];
+    int e = min(b, seg[n + 1]);
+    for (;;) {
+      // the next segment's force density, loaded beside this one's sources
+      const int64_t nn = n + 1 < N ? n + 1 : n;
+      const double hx = f[nn], hy = f[N + nn], hz = f[2 * N + nn];
+      const int en = seg[nn + 1];
+#pragma unroll 2
+      for (; p < e; ++p) {
+        const double4 s = X64[p];
+        const double rx = px - s.x, ry = py - s.y, rz = pz - s.z;
+        const double d = fma(rz, rz, fma(ry, ry, fma(rx, rx, eps2)));
+        const double r = rsqrt_refined(d);                // (|r|^2 + eps^2)^(-1/2)
+        const double wr = s.w * r;
+        const double t = wr * (r * r);                    // w (|r|^2 + eps^2)^(-3/2)
+        const double rg = fma(rz, gz, fma(ry, gy, rx * gx));
+        const double al = fma(t, eps2, wr);               // (|r|^2 + 2 eps^2) t
+        const double be = t * rg;
+        ux = fma(al, gx, fma(be, rx, ux));
+        uy = fma(al, gy, fma(be, ry, uy));
+        uz = fma(al, gz, fma(be, rz, uz));
+      }
+      if (p >= b) break;
+      n = n + 1;
+      gx = hx;
+      gy = hy;
+      gz = hz;
+      e = min(b, en);
+    }
+  }
+  red[0][w][lane] = ux;
+  red[1][w][lane] = uy;
+  red[2][w][lane] = uz;
+  __syncthreads();
+  if (w < 3 && m < N) {
+    double acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < kPairWaves; ++k) acc += red[w][k][lane];
+    part[(int64_t)ch * 3 * N + w * N + m] = acc;
+  }
+}
+
 constexpr int kApplyThreads = 256;
 
 // Stage 2 for the 3N velocity rows: sum the chunks in a fixed order (wave w
@@ -418,22 +518,37 @@ hipError_t launch_rhs(int64_t N, int32_t M, const double* u, const double* ftext
   return hipGetLastError();
 }
 
+// Chunks of the pair sum: 2048 workgroups (eight per CU) while the sources give
+// every chunk at least kMinChunk of them.
+FieldPlan apply_plan(int64_t N, int64_t Q) {
+  constexpr int64_t kMinChunk = 96;
+  FieldPlan fp;
+  fp.pblocks = (N + 63) / 64;
+  int64_t c = 2048 / std::max<int64_t>(fp.pblocks, 1);
+  c = std::min<int64_t>(c, std::max<int64_t>(1, Q / kMinChunk));
+  c = std::max<int64_t>(1, std::min<int64_t>(c, 1024));
+  if (c >= 8) c -= c % 8;  // whole rounds of the eight XCDs
+  fp.cap = (int32_t)c;
+  fp.chunk = (Q + c - 1) / c;
+  fp.chunks = (int32_t)((Q + fp.chunk - 1) / fp.chunk);
+  return fp;
+}
+
 // Matrix-free FP64 product: the velocity rows are the flow of the force
-// densities v at the force points (the field pair sum of field.hip with the
-// N force points as field points: sources w_q v[nu(q)] gathered once, chunk
-// partial sums), then the fixed-order chunk sum with the rigid-body motion
-// and the balance rows in one launch (k_apply_stage2).  `chunks` bounds the
-// partial buffer (at least field_plan(N, Q).cap).
+// densities v at the force points (chunk partial sums over the nu-sorted sources),
+// then the fixed-order chunk sum with the rigid-body motion and the balance rows
+// in one launch (k_apply_stage2).  `chunks` bounds the partial buffer (at least
+// apply_plan(N, Q).cap).
 hipError_t launch_apply(const nrs_problem& pb, const Sorted& srt, const double* v, double* y,
                         double* part, int32_t chunks, const int32_t* stop, hipStream_t s) {
   const int64_t N = pb.N, Q = pb.Q;
   if (N > 0) {
-    const FieldPlan fp = field_plan(N, Q);
+    const FieldPlan fp = apply_plan(N, Q);
     if (fp.chunks > chunks) return hipErrorInvalidValue;
-    hipError_t e = launch_field_sources(N, Q, pb.X, pb.w, pb.nu, v, srt.fsrc, s, stop);
-    if (e != hipSuccess) return e;
-    e = launch_field_part(fp, N, Q, pb.x, nullptr, 0.0, srt.fsrc, pb.eps, part, s, stop);
-    if (e != hipSuccess) return e;
+    const int64_t slots = fp.chunks >= 8 ? 8 * ((fp.chunks + 7) / 8) : fp.chunks;
+    hipLaunchKernelGGL(k_apply_pairs, dim3((unsigned)(fp.pblocks * slots)), dim3(kPairThreads), 0,
+                       s, N, fp.pblocks, fp.chunks, fp.chunk, pb.x, srt.seg, srt.nus, srt.X64, v,
+                       pb.eps * pb.eps, part, stop);
     const unsigned blocks = (unsigned)((3 * N + 63) / 64 + pb.M);
     hipLaunchKernelGGL(k_apply_stage2, dim3(blocks), dim3(kApplyThreads), 0, s, N, pb.M,
                        fp.chunks, part, 1.0 / (8.0 * kPi * pb.mu), pb.x, pb.body, pb.Y, srt.W, v,

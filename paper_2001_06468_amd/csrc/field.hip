@@ -23,23 +23,11 @@ namespace {
 constexpr int kFieldThreads = 256;  // four waves, one field point per lane
 constexpr int kFieldWaves = kFieldThreads / 64;
 
-// 1/sqrt(d) for d > 0: the hardware estimate r0 (relative error about
-// 2^-23) corrected by the series (1 - e)^(-1/2) = 1 + e/2 + 3e^2/8 + O(e^3)
-// with e = 1 - d r0^2, i.e. one third-order step; the neglected terms are
-// about 2^-69, so the result is within rounding of the correctly rounded value.
-__device__ inline double rsqrt_refined(double d) {
-  const double r0 = __builtin_amdgcn_rsq(d);
-  const double e = fma(-(d * r0), r0, 1.0);
-  return fma(r0 * e, fma(e, 0.375, 0.5), r0);
-}
-
 // Eight lanes per record, one double each, so that consecutive lanes store
 // consecutive doubles.
 __global__ void k_field_sources(int64_t N, int64_t Q, const double* __restrict__ X,
                                 const double* __restrict__ w, const int32_t* __restrict__ nu,
-                                const double* __restrict__ f, double* __restrict__ src,
-                                const int32_t* __restrict__ stop) {
-  if (stop && *stop) return;
+                                const double* __restrict__ f, double* __restrict__ src) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t q = i >> 3;
   const int k = (int)(i & 7);
@@ -65,9 +53,7 @@ __global__ void k_field_sources(int64_t N, int64_t Q, const double* __restrict__
 __global__ __launch_bounds__(kFieldThreads) void k_field_part(
     int64_t P, int64_t Q, int64_t pblocks, int32_t chunks, int64_t chunk,
     const double* __restrict__ y, const double* __restrict__ K, double c,
-    const FieldSrc* __restrict__ src, double eps2, double* __restrict__ part,
-    const int32_t* __restrict__ stop) {
-  if (stop && *stop) return;
+    const FieldSrc* __restrict__ src, double eps2, double* __restrict__ part) {
   __shared__ double red[3][kFieldWaves][64];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -190,20 +176,9 @@ FieldPlan field_plan(int64_t P, int64_t Q) {
 
 hipError_t launch_field_sources(int64_t N, int64_t Q, const double* X, const double* w,
                                 const int32_t* nu, const double* f, FieldSrc* src,
-                                hipStream_t s, const int32_t* stop) {
+                                hipStream_t s) {
   hipLaunchKernelGGL(k_field_sources, dim3((unsigned)((8 * Q + 255) / 256)), dim3(256), 0, s, N, Q,
-                     X, w, nu, f, reinterpret_cast<double*>(src), stop);
-  return hipGetLastError();
-}
-
-hipError_t launch_field_part(const FieldPlan& fp, int64_t P, int64_t Q, const double* y,
-                             const double* K, double c, const FieldSrc* src, double eps,
-                             double* part, hipStream_t s, const int32_t* stop) {
-  if (P <= 0) return hipSuccess;
-  const int64_t slots = fp.chunks >= 8 ? 8 * ((fp.chunks + 7) / 8) : fp.chunks;
-  const unsigned grid = (unsigned)(fp.pblocks * slots);
-  hipLaunchKernelGGL(k_field_part, dim3(grid), dim3(kFieldThreads), 0, s, P, Q, fp.pblocks,
-                     fp.chunks, fp.chunk, y, K, c, src, eps * eps, part, stop);
+                     X, w, nu, f, reinterpret_cast<double*>(src));
   return hipGetLastError();
 }
 
@@ -211,8 +186,9 @@ hipError_t launch_field(const FieldPlan& fp, int64_t P, int64_t Q, const double*
                         const double* K, double c, const FieldSrc* src, double eps, double mu,
                         double* part, double* u, hipStream_t s) {
   if (P <= 0) return hipSuccess;
-  hipError_t e = launch_field_part(fp, P, Q, y, K, c, src, eps, part, s, nullptr);
-  if (e != hipSuccess) return e;
+  const int64_t slots = fp.chunks >= 8 ? 8 * ((fp.chunks + 7) / 8) : fp.chunks;
+  hipLaunchKernelGGL(k_field_part, dim3((unsigned)(fp.pblocks * slots)), dim3(kFieldThreads), 0, s,
+                     P, Q, fp.pblocks, fp.chunks, fp.chunk, y, K, c, src, eps * eps, part);
   hipLaunchKernelGGL(k_field_sum, dim3((unsigned)((3 * P + 63) / 64)), dim3(kSumWaves * 64), 0, s,
                      3 * P, fp.chunks, part, 1.0 / (8.0 * kPi * mu), u);
   return hipGetLastError();

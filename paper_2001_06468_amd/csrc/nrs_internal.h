@@ -156,7 +156,6 @@ struct Sorted {
   float4* X32lo;     // [Q] (x_lo, y_lo, z_lo, 0): x = x_hi + x_lo to FP32 x FP32 precision
   double* W;         // [N] patch weights
   int32_t* cnt;      // [N+2] scratch; cnt[N+1] counts quadrature points with nu out of range
-  FieldSrc* fsrc;    // [Q] source records of the matrix-free product (original order)
 };
 
 // All device buffers of one solve, carved from the workspace.
@@ -549,6 +548,16 @@ hipError_t launch_rk_lincomb(int64_t n, const double* Y, const RkComb& cb, doubl
 hipError_t launch_dp_error(int64_t n, const double* Y, const double* Yn, const RkComb& cb, double h,
                            double rtol, double atol, double* out, hipStream_t s);
 
+// 1/sqrt(d) for d > 0: the hardware estimate r0 (relative error about
+// 2^-23) corrected by the series (1 - e)^(-1/2) = 1 + e/2 + 3e^2/8 + O(e^3)
+// with e = 1 - d r0^2, i.e. one third-order step; the neglected terms are
+// about 2^-69, so the result is within rounding of the correctly rounded value.
+__device__ inline double rsqrt_refined(double d) {
+  const double r0 = __builtin_amdgcn_rsq(d);
+  const double e = fma(-(d * r0), r0, 1.0);
+  return fma(r0 * e, fma(e, 0.375, 0.5), r0);
+}
+
 // flow at field points and tracers
 
 // Field points in blocks of 64 (one per lane), sources cut into `chunks`
@@ -560,13 +569,10 @@ struct FieldPlan {
   int32_t chunks, cap;
 };
 FieldPlan field_plan(int64_t P, int64_t Q);
+// the same for the pair sum of the matrix-free product (P = N force points)
+FieldPlan apply_plan(int64_t N, int64_t Q);
 hipError_t launch_field_sources(int64_t N, int64_t Q, const double* X, const double* w,
-                                const int32_t* nu, const double* f, FieldSrc* src, hipStream_t s,
-                                const int32_t* stop = nullptr);
-// chunk partial sums part[chunk][3][P] of the flow at y + c K (unscaled)
-hipError_t launch_field_part(const FieldPlan& fp, int64_t P, int64_t Q, const double* y,
-                             const double* K, double c, const FieldSrc* src, double eps,
-                             double* part, hipStream_t s, const int32_t* stop);
+                                const int32_t* nu, const double* f, FieldSrc* src, hipStream_t s);
 // u [3][P] = flow of the sources at y + c K (K may be NULL: at y)
 hipError_t launch_field(const FieldPlan& fp, int64_t P, int64_t Q, const double* y,
                         const double* K, double c, const FieldSrc* src, double eps, double mu,
