@@ -297,71 +297,6 @@ __global__ __launch_bounds__(kScanBlock) void k_csr_scan(int64_t N, int32_t* cnt
   if (tid == kScanBlock - 1) seg[N] = total;
 }
 
-// Count, scan and scatter in one workgroup with the counters in LDS, for
-// N <= kCsrSmallN and Q <= kCsrSmallQ (the single-system workloads): the
-// same segments (seg) as the three-kernel path; the order inside a segment
-// is arbitrary until k_csr_finish sorts it.
-constexpr int64_t kCsrSmallN = 8192;
-constexpr int64_t kCsrSmallQ = 1 << 17;
-// loads in flight per thread (the one workgroup is bound by their latency): 32,000
-// points 21 -> 11.7 us.  Measured slower: one atomic per run of equal nu, found
-// by lane shuffles (10.7 against 8.2 us at 10,000 points) or by consecutive points per
-// thread (68 against 25 us at 40,000).
-constexpr int kCsrBatch = 8;
-__global__ __launch_bounds__(kScanBlock) void k_csr_small(int64_t N, int64_t Q,
-                                                          const int32_t* __restrict__ nu,
-                                                          int32_t* __restrict__ seg,
-                                                          int32_t* __restrict__ perm,
-                                                          SolveState* st) {
-  __shared__ int32_t c[kCsrSmallN + 2];
-  __shared__ int32_t wtot[kScanBlock / 64];
-  const int tid = threadIdx.x;
-  for (int64_t i = tid; i < N + 2; i += kScanBlock) c[i] = 0;
-  __syncthreads();
-  for (int64_t q = tid; q < Q; q += kCsrBatch * kScanBlock) {
-    int32_t v[kCsrBatch];
-#pragma unroll
-    for (int e = 0; e < kCsrBatch; ++e) {
-      const int64_t qe = q + e * kScanBlock;
-      v[e] = qe < Q ? nu[qe] : -2;
-    }
-#pragma unroll
-    for (int e = 0; e < kCsrBatch; ++e)
-      if (q + e * kScanBlock < Q) atomicAdd(&c[(v[e] >= 0 && v[e] < N) ? v[e] : N + 1], 1);
-  }
-  __syncthreads();
-  if (tid == 0 && st && c[N + 1] > 0) {
-    st->nonfinite = 2;
-    st->failed = 1;
-    st->stop = 1;
-  }
-  const int64_t per = (N + kScanBlock - 1) / kScanBlock;
-  const int64_t a = tid * per, b = min<int64_t>(N, a + per);
-  int32_t sum = 0;
-  for (int64_t i = a; i < b; ++i) sum += c[i];
-  int32_t total;
-  int32_t run = block_exclusive_scan(sum, wtot, &total);
-  for (int64_t i = a; i < b; ++i) {
-    const int32_t k = c[i];
-    seg[i] = run;
-    c[i] = run;
-    run += k;
-  }
-  if (tid == kScanBlock - 1) seg[N] = total;
-  __syncthreads();
-  for (int64_t q = tid; q < Q; q += kCsrBatch * kScanBlock) {
-    int32_t v[kCsrBatch];
-#pragma unroll
-    for (int e = 0; e < kCsrBatch; ++e) {
-      const int64_t qe = q + e * kScanBlock;
-      v[e] = qe < Q ? nu[qe] : -1;
-    }
-#pragma unroll
-    for (int e = 0; e < kCsrBatch; ++e)
-      if (v[e] >= 0 && v[e] < N) perm[atomicAdd(&c[v[e]], 1)] = (int32_t)(q + e * kScanBlock);
-  }
-}
-
 __global__ void k_csr_scatter(int64_t N, int64_t Q, const int32_t* __restrict__ nu,
                               int32_t* cursor, int32_t* perm) {
   const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -453,6 +388,164 @@ __global__ __launch_bounds__(kFinishWaves * 64) void k_csr_finish(
   if (lane == 0) W[n] = wsum;
 }
 
+// The whole layout in one launch for N <= kCsrSmallN and Q <= kCsrSmallQ: a workgroup
+// owns kSegPts consecutive force points, reads every nu, counts the points of
+// lower force points (its place in the layout, so workgroups need nothing from
+// each other) and lists its own in order of their index, which is the order of the
+// layout: nothing is sorted.  Every wave takes a contiguous share of the
+// quadrature points and keeps its list in LDS (kSegCap entries; a wave that finds
+// more reads its share a second time instead).
+// What bounds it: the latency of reading nu, eight loads in flight per lane.
+// A count, scan and scatter in one workgroup followed by a sort per force
+// point took 8.2 + 4.7 us for 10,000 points (10.8 us so) and 25 + 6 us for 40,000
+// (15.8 us so).
+constexpr int64_t kCsrSmallN = 8192;
+constexpr int64_t kCsrSmallQ = 1 << 17;
+constexpr int kSegPts = 16;
+constexpr int kSegWaves = 16;
+constexpr int kSegCap = 512;
+constexpr int kSegBatch = 8;
+constexpr int kSegW = 64;
+
+__global__ __launch_bounds__(kSegWaves * 64) void k_csr_segments(
+    int64_t N, int64_t Q, const int32_t* __restrict__ nu, const double* __restrict__ X,
+    const double* __restrict__ w, int32_t* __restrict__ seg, int32_t* __restrict__ perm,
+    int32_t* __restrict__ nus, double4* __restrict__ X64, float4* __restrict__ X32hi,
+    float4* __restrict__ X32lo, double* __restrict__ W, SolveState* st) {
+  __shared__ int32_t list[kSegWaves][kSegCap];    // q + (force point - n0) 2^20
+  __shared__ int16_t rank[kSegWaves][kSegCap];    // place among the wave's of that force point
+  __shared__ int32_t cnt[kSegWaves][kSegPts];     // members, then where each wave's start
+  __shared__ double sw[kSegPts][kSegW];           // weights by place (short segments)
+  __shared__ int32_t below[kSegWaves], len[kSegWaves];
+  __shared__ int32_t base[kSegPts + 1];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t lower = (1ull << lane) - 1;
+  const int32_t n0 = (int32_t)blockIdx.x * kSegPts;
+  const int32_t n1 = (int32_t)min<int64_t>(N, n0 + kSegPts);
+  const int32_t per = ((int32_t)Q + kSegWaves * 64 - 1) / (kSegWaves * 64) * 64;
+  const int32_t qa = min((int32_t)Q, wv * per), qb = min((int32_t)Q, qa + per);
+  // calls f(q, nu[q] or N past the share) for the 64 points from q on, for all of them
+  auto scan = [&](auto f) {
+    for (int32_t q = qa; q < qb; q += 64 * kSegBatch) {
+      int32_t v[kSegBatch];
+#pragma unroll
+      for (int e = 0; e < kSegBatch; ++e) {
+        const int32_t qe = q + 64 * e + lane;
+        v[e] = qe < qb ? nu[qe] : (int32_t)N;
+      }
+#pragma unroll
+      for (int e = 0; e < kSegBatch; ++e) f(q + 64 * e + lane, v[e]);
+    }
+  };
+  int32_t lo = 0, found = 0, bad = 0;   // wave-uniform (but bad)
+  int32_t next = 0;   // lane k < kSegPts: members of force point n0 + k so far
+  scan([&](int32_t q, int32_t v) {
+    lo += __popcll(__ballot(v >= 0 && v < n0));
+    const bool hit = v >= n0 && v < n1;
+    bad |= q < qb && (v < 0 || v >= N);
+    const uint64_t m = __ballot(hit);
+    if (m) {
+      const int at = found + __popcll(m & lower);
+      int32_t before = 0;
+      for (uint64_t left = m; left;) {   // one force point at a time
+        const int32_t k = __builtin_amdgcn_readlane(v, __builtin_ctzll(left));
+        const uint64_t mk = __ballot(hit && v == k);
+        if (v == k) before = __builtin_amdgcn_readlane(next, k - n0) + __popcll(mk & lower);
+        if (lane == k - n0) next += __popcll(mk);
+        left &= ~mk;
+      }
+      if (hit && at < kSegCap) {
+        list[wv][at] = q | (v - n0) << 20;
+        rank[wv][at] = (int16_t)before;
+      }
+      found += __popcll(m);
+    }
+  });
+  if (lane < kSegPts) cnt[wv][lane] = next;
+  if (lane == 0) {
+    below[wv] = lo;
+    len[wv] = found;
+  }
+  if (blockIdx.x == 0 && st && bad) {
+    st->nonfinite = 2;
+    st->failed = 1;
+    st->stop = 1;
+  }
+  __syncthreads();
+  if (wv == 0) {
+    int32_t first = 0, mine = 0;
+#pragma unroll
+    for (int k = 0; k < kSegWaves; ++k) {
+      first += below[k];
+      if (lane < kSegPts) mine += cnt[k][lane];
+    }
+    int32_t incl = mine;
+#pragma unroll
+    for (int o = 1; o < kSegPts; o <<= 1) {
+      const int32_t y = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += y;
+    }
+    if (lane < kSegPts) {
+      int32_t at = first + incl - mine;
+      base[lane] = at;
+      if (n0 + lane < n1) seg[n0 + lane] = at;
+      if (lane == kSegPts - 1) base[kSegPts] = at + mine;
+      if (n0 + lane == N - 1) seg[N] = at + mine;
+#pragma unroll
+      for (int k = 0; k < kSegWaves; ++k) {
+        const int32_t c = cnt[k][lane];
+        cnt[k][lane] = at;
+        at += c;
+      }
+    }
+  }
+  __syncthreads();
+  // every thread stores records of every list (a force point's members mostly lie in
+  // one wave's share)
+  const int32_t lens = len[lane & (kSegWaves - 1)];
+  const bool tooLong = __any(lens > kSegCap);
+#pragma unroll 1
+  for (int k = 0; k < kSegWaves; ++k) {
+    const int32_t c = __builtin_amdgcn_readlane(lens, k);
+    if (c > kSegCap) continue;
+    for (int32_t i = threadIdx.x; i < c; i += kSegWaves * 64) {
+      const int32_t v = list[k][i], p = v >> 20, at = cnt[k][p] + rank[k][i];
+      const double wq = csr_store(Q, n0 + p, at, v & ((1 << 20) - 1), X, w, perm, nus, X64, X32hi,
+                                  X32lo);
+      if (at - base[p] < kSegW) sw[p][at - base[p]] = wq;
+    }
+  }
+  if (found > kSegCap) {   // this wave's list was too short: its share once more
+    next = lane < kSegPts ? cnt[wv][lane] : 0;
+    scan([&](int32_t q, int32_t v) {
+      const bool hit = v >= n0 && v < n1;
+      for (uint64_t left = __ballot(hit); left;) {
+        const int32_t k = __builtin_amdgcn_readlane(v, __builtin_ctzll(left));
+        const uint64_t mk = __ballot(hit && v == k);
+        const int32_t at = __builtin_amdgcn_readlane(next, k - n0) + __popcll(mk & lower);
+        if (hit && v == k)
+          csr_store(Q, k, at, q, X, w, perm, nus, X64, X32hi, X32lo);
+        if (lane == k - n0) next += __popcll(mk);
+        left &= ~mk;
+      }
+    });
+  }
+  const int32_t longest = base[min(lane, kSegPts - 1) + 1] - base[min(lane, kSegPts - 1)];
+  const bool fromLds = !tooLong && !__any(longest > kSegW);   // the same in every wave
+  if (!fromLds) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's records are stored
+  __syncthreads();
+  // patch weights: lane l adds places l, l + 64, ...; then a fixed tree over lanes
+  for (int k = wv; k < n1 - n0; k += kSegWaves) {
+    double sum = 0.0;
+    const int32_t c = base[k + 1] - base[k];
+    for (int32_t i = lane; i < c; i += 64) sum += fromLds ? sw[k][i] : X64[base[k] + i].w;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (lane == 0) W[n0 + k] = sum;
+  }
+}
+
 inline dim3 grid1(int64_t n, int b) { return dim3((unsigned)((n + b - 1) / b)); }
 
 }  // namespace
@@ -495,19 +588,20 @@ hipError_t launch_fill_f64(double* p, double v, int64_t n, hipStream_t s) {
 hipError_t launch_build_csr(int64_t N, int64_t Q, const double* X, const double* w,
                             const int32_t* nu, Sorted& srt, SolveState* st, hipStream_t s) {
   if (N <= kCsrSmallN && Q <= kCsrSmallQ) {
-    hipLaunchKernelGGL(k_csr_small, dim3(1), dim3(kScanBlock), 0, s, N, Q, nu, srt.seg, srt.perm,
-                       st);
-  } else {
-    hipError_t e = launch_fill_i32(srt.cnt, 0, N + 2, s);
-    if (e != hipSuccess) return e;
-    if (Q > 0) {
-      hipLaunchKernelGGL(k_csr_count, grid1(Q, 256), dim3(256), 0, s, N, Q, nu, srt.cnt);
-    }
-    hipLaunchKernelGGL(k_csr_scan, dim3(1), dim3(kScanBlock), 0, s, N, srt.cnt, srt.seg, st);
-    if (Q > 0) {
-      hipLaunchKernelGGL(k_csr_scatter, grid1(Q, 256), dim3(256), 0, s, N, Q, nu, srt.cnt,
-                         srt.perm);
-    }
+    hipLaunchKernelGGL(k_csr_segments, dim3((unsigned)((N + kSegPts - 1) / kSegPts)),
+                       dim3(kSegWaves * 64), 0, s, N, Q, nu, X, w, srt.seg, srt.perm, srt.nus,
+                       srt.X64, srt.X32hi, srt.X32lo, srt.W, st);
+    return hipGetLastError();
+  }
+  hipError_t e = launch_fill_i32(srt.cnt, 0, N + 2, s);
+  if (e != hipSuccess) return e;
+  if (Q > 0) {
+    hipLaunchKernelGGL(k_csr_count, grid1(Q, 256), dim3(256), 0, s, N, Q, nu, srt.cnt);
+  }
+  hipLaunchKernelGGL(k_csr_scan, dim3(1), dim3(kScanBlock), 0, s, N, srt.cnt, srt.seg, st);
+  if (Q > 0) {
+    hipLaunchKernelGGL(k_csr_scatter, grid1(Q, 256), dim3(256), 0, s, N, Q, nu, srt.cnt,
+                       srt.perm);
   }
   hipLaunchKernelGGL(k_csr_finish, dim3((unsigned)((N + kFinishWaves - 1) / kFinishWaves)),
                      dim3(kFinishWaves * 64), 0, s, N, Q, srt.seg, srt.perm, X, w, srt.nus, srt.X64,
