@@ -999,6 +999,7 @@ nrs_status nrs_autotune(nrs_ctx* ctx, const nrs_problem* pb, void* ws, size_t ws
   NRS_HIP(ctx, hipEventCreate(&e1));
   int32_t best[2] = {kAsmDefaultShape, kAsmDefaultShape};
   float best_ms[2] = {0.f, 0.f}, def_ms[2] = {0.f, 0.f};
+  int32_t record[2] = {-1, -1};   // shape used from now on: the best, or the size's own
   hipError_t err = hipSuccess;
   // per shape: one warm-up launch, then the best of three timed runs of
   // kLaunches back-to-back launches (one event pair around each run, so that
@@ -1009,18 +1010,25 @@ nrs_status nrs_autotune(nrs_ctx* ctx, const nrs_problem* pb, void* ws, size_t ws
                      : launch_assemble<double>(*pb, sb.srt, sb.A64, sb.lda, s, shape);
   };
   for (int prec = 0; prec < 2 && err == hipSuccess; ++prec) {
-    for (int shape = 0; shape < kAsmShapes && err == hipSuccess; ++shape) {
-      err = launch(prec, shape);
+    // the candidates, then (shape kAsmShapes here) the untuned shape of this size
+    for (int shape = 0; shape <= kAsmShapes && err == hipSuccess; ++shape) {
+      const bool own = shape == kAsmShapes;
+      err = launch(prec, own ? -1 : shape);
       float avg = 0.f;
       for (int rep = 0; rep < 3 && err == hipSuccess; ++rep) {
         err = hipEventRecord(e0, s);
-        for (int k = 0; k < kLaunches && err == hipSuccess; ++k) err = launch(prec, shape);
+        for (int k = 0; k < kLaunches && err == hipSuccess; ++k)
+          err = launch(prec, own ? -1 : shape);
         if (err == hipSuccess) err = hipEventRecord(e1, s);
         if (err == hipSuccess) err = hipEventSynchronize(e1);
         float ms = 0.f;
         if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
         const float per = ms / kLaunches;
         if (rep == 0 || per < avg) avg = per;
+      }
+      if (own) {
+        record[prec] = avg < best_ms[prec] ? -1 : best[prec];
+        continue;
       }
       if (shape == kAsmDefaultShape) def_ms[prec] = avg;
       if (shape == 0 || avg < best_ms[prec]) {
@@ -1036,11 +1044,11 @@ nrs_status nrs_autotune(nrs_ctx* ctx, const nrs_problem* pb, void* ws, size_t ws
   bool found = false;
   for (auto& e : ctx->tune)
     if (e.cls == c) {
-      e.shape32 = best[0];
-      e.shape64 = best[1];
+      e.shape32 = record[0];
+      e.shape64 = record[1];
       found = true;
     }
-  if (!found) ctx->tune.push_back({c, best[0], best[1]});
+  if (!found) ctx->tune.push_back({c, record[0], record[1]});
   if (out) {
     out->size_class = c;
     asm_shape_dims(best[0], &out->block32, &out->strip32);

@@ -22,6 +22,17 @@ namespace {
 // autotuner) never changes a result.
 constexpr int kShapeBlk[kAsmShapes] = {64, 64, 64, 128, 128, 128, 256, 256, 256};
 constexpr int kShapeTN[kAsmShapes] = {4, 8, 16, 4, 8, 16, 4, 8, 16};
+// Shape of a problem that is not tuned, by force points: small matrices leave
+// SIMDs idle unless every strip is one force point (64 rows x 1 point, shape
+// kAsmShapes, not a candidate of the autotuner), the largest want few, long
+// workgroups.  Measured, us, FP32 / FP64, against 128 rows x 8 points: N = 40 3.3 /
+// 3.3 (12.2 / 13.2), N = 480 6.4 / 7.9 (15.3 / 16.8), N = 1000 13.1 / 18.6 (20.2 /
+// 27.2), N = 1920 64 x 1 34.1 / 56.0, 128 x 4 34.6 / 52.6 (36.0 / 61.4), N = 4000
+// 128 x 4 184 / 293, 256 x 4 172 / 296 (189 / 292).
+inline int asm_untuned_shape(int64_t N) {
+  if (N <= 1536) return kAsmShapes;
+  return N <= 3072 ? 3 : 6;
+}
 
 // Component j of e_i x r.
 __device__ inline double cross_unit(int i, int j, const double r[3]) {
@@ -190,7 +201,7 @@ __global__ __launch_bounds__(kAsmBlock) void k_assemble64(
       const double4 q = X64[p];
       const double rx = px - q.x, ry = py - q.y, rz = pz - q.z;
       const double d = rx * rx + ry * ry + rz * rz + eps2;
-      const double rho = 1.0 / sqrt(d);
+      const double rho = rsqrt_refined(d);
       const double t = q.w * (rho * rho * rho);
       const double s = (d + eps2) * t;
       const double tx = t * rx, ty = t * ry, tz = t * rz;
@@ -463,6 +474,7 @@ void asm_dispatch(int shape, const nrs_problem& pb, const Sorted& srt, T* A, int
                   hipStream_t s);
 #define NRS_ASM_CASES(F)                                                                        \
   switch (shape) {                                                                             \
+    case kAsmShapes: F<64, 1>(pb, srt, A, lda, scale, s); break;                               \
     case 0: F<64, 4>(pb, srt, A, lda, scale, s); break;                                        \
     case 1: F<64, 8>(pb, srt, A, lda, scale, s); break;                                        \
     case 2: F<64, 16>(pb, srt, A, lda, scale, s); break;                                       \
@@ -501,6 +513,7 @@ hipError_t launch_assemble(const nrs_problem& pb, const Sorted& srt, T* A, int64
   const T scale = (T)(1.0 / (8.0 * kPi * pb.mu));
   // one launch: the fused operator and, in extra workgroups, the rigid-body
   // rows and columns
+  if (shape < 0) shape = asm_untuned_shape(N);
   if (N > 0) asm_dispatch<T>(shape, pb, srt, A, lda, scale, s);
   (void)n;
   return hipGetLastError();

@@ -423,9 +423,9 @@ hipError_t launch_nearest(int64_t N, const double* x, const GroupTable& gt, int6
 hipError_t launch_build_csr(int64_t N, int64_t Q, const double* X, const double* w,
                             const int32_t* nu, Sorted& srt, SolveState* st, hipStream_t s);
 // Assembly launch shapes: shape index -> (rows per workgroup, force points
-// per strip); -1 = default.  Results do not depend on the shape.
+// per strip); -1 = by the problem's size.  Results do not depend on the shape.
 constexpr int kAsmShapes = 9;
-constexpr int kAsmDefaultShape = 4;   // 128 rows, 8 force points
+constexpr int kAsmDefaultShape = 4;   // 128 rows, 8 force points (the autotuner's yardstick)
 void asm_shape_dims(int32_t shape, int32_t* blk, int32_t* tn);
 template <class T>
 hipError_t launch_assemble(const nrs_problem& pb, const Sorted& srt, T* A, int64_t lda,

@@ -58,3 +58,10 @@ def test_layout_past_the_one_launch_form():
     rng = np.random.default_rng(3)
     Q = (1 << 17) + 5
     _check(12, Q, rng.integers(0, 12, size=Q).astype(np.int32))
+
+
+# force points on both sides of the lines between the untuned assembly shapes
+@pytest.mark.parametrize("N", [1536, 1537, 3073])
+def test_assembly_shapes(N):
+    rng = np.random.default_rng(N)
+    _check(N, 2 * N, rng.integers(0, N, size=2 * N).astype(np.int32))
