@@ -799,6 +799,69 @@ __global__ __launch_bounds__(kTrsvThreads) void k_trsv(TrsvBatch<T> bt, int32_t*
   }
 }
 
+// Inverse of the lower (unit diagonal) or upper triangle of the 64 x 64 block d, its
+// column c in column pc[c] of x; four waves, ends with a barrier.  Wave w inverts the
+// 16 x 16 diagonal block w by substitution on the identity (one lane per column, in
+// FP64, rounded once); then the blocks at distance 1, 2, 3 from the diagonal follow
+// on the matrix cores, X_ij = -X_ii sum_k T_ik X_kj, one block per wave.  The products
+// take their 16 terms in the order 4g + s (lane group g, step s), so the inner sum's
+// output registers are the outer product's operand as they are.
+// One wave substituting through all 64 rows took most of the 24 us of a two-block
+// solve (n = 126); so it takes 20 us, and both passes at n = 3150 131 -> 127 us.
+template <bool UP>
+__device__ inline void invert_tri64(const float (*d)[kTb + 4], float (*x)[kTb + 1], const int* pc,
+                                    int w, int lane) {
+  typedef float floatx4 __attribute__((ext_vector_type(4)));
+  const int l = lane & 15, g = lane >> 4, o = 16 * w;
+  if (lane < 16) {
+    double c[16];
+    const double rd = UP ? 1.0 / (double)d[o + lane][o + lane] : 1.0;
+#pragma unroll
+    for (int ii = 0; ii < 16; ++ii) {
+      const int i = UP ? 15 - ii : ii;
+      double v = i == lane ? 1.0 : 0.0;
+#pragma unroll
+      for (int kk = 0; kk < ii; ++kk) {
+        const int k = UP ? 15 - kk : kk;
+        v = fma(-(double)d[o + i][o + k], c[k], v);
+      }
+      c[i] = UP ? v * bcast_lane(rd, i) : v;
+    }
+    const int col = pc[o + lane];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[o + i][col] = (float)c[i];
+  } else {
+    // the zero blocks on the other side of the diagonal: rows of block w
+    for (int e = lane - 16; e < 16 * kTb; e += 48) {
+      const int i = e & 15, c = e >> 4;
+      if (UP ? (c >> 4) < w : (c >> 4) > w) x[o + i][pc[c]] = 0.f;
+    }
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int dist = 1; dist < 4; ++dist) {
+    const int i = UP ? w : w + dist, j = UP ? w + dist : w;
+    if (w + dist < 4) {
+      const int cj = pc[16 * j + l];
+      floatx4 t = {0.f, 0.f, 0.f, 0.f};
+      for (int k = UP ? i + 1 : j; k < (UP ? j + 1 : i); ++k) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          t = __builtin_amdgcn_mfma_f32_16x16x4f32(d[16 * i + l][16 * k + 4 * g + s],
+                                                   x[16 * k + 4 * g + s][cj], t, 0, 0, 0);
+      }
+      floatx4 r = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        r = __builtin_amdgcn_mfma_f32_16x16x4f32(x[16 * i + l][pc[16 * i + 4 * g + s]], t[s], r, 0,
+                                                 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[16 * i + 4 * g + q][cj] = -r[q];
+    }
+    __syncthreads();
+  }
+}
+
 // FP32 triangular solves.  Block row b (64 rows) is solved by one workgroup
 // as x_b = c_b - M_b x_l, where l is the block solved just before it (b - 1
 // for the lower pass, b + 1 for the upper), D_b the diagonal block (unit
@@ -827,6 +890,7 @@ __global__ __launch_bounds__(kTrsvThreads) void k_trsv32(TrsvBatch<float> bt,
   // inversion) and D^-1 (odd stride for the column reads that follow)
   __shared__ __align__(16) float s_d[kTb][kTb + 4];
   __shared__ float s_di[kTb][kLd];
+  __shared__ int s_pc[kTb];        // column of s_di that holds column c of D^-1
   __shared__ float s_l[kTb][kLd];  // A_bl (row-major), then M
   __shared__ float s_w[kTrsvThreads / 64][16];  // per-wave copy of the polled values
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -884,52 +948,14 @@ __global__ __launch_bounds__(kTrsvThreads) void k_trsv32(TrsvBatch<float> bt,
       s_d[i][c] = v;
     }
     __syncthreads();
-    if (w == 0) {
-      // the lower pass of the tile LU's factors applies the block row's
-      // interchanges first: (D^-1 P)[i][p(c)] = D^-1[i][c]
-      const int pc = (LOCALP && !UPPER && lane < rows) ? sy.perm[row] - (int)r0 : lane;
-      float xc[kTb];  // column `lane` of D^-1
-      if (!UPPER) {
-        // unit lower: X[i][c] = [i == c] - sum_{k < i} L[i][k] X[k][c]
-#pragma unroll
-        for (int i = 0; i < kTb; ++i) {
-          float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-#pragma unroll
-          for (int k = 0; k + 3 < i; k += 4) {
-            s0 += s_d[i][k] * xc[k];
-            s1 += s_d[i][k + 1] * xc[k + 1];
-            s2 += s_d[i][k + 2] * xc[k + 2];
-            s3 += s_d[i][k + 3] * xc[k + 3];
-          }
-#pragma unroll
-          for (int k = i & ~3; k < i; ++k) s0 += s_d[i][k] * xc[k];
-          const float sum = (s0 + s1) + (s2 + s3);
-          xc[i] = i < lane ? 0.f : (i == lane ? 1.f : -sum);
-        }
-      } else {
-        // upper: X[i][c] = ([i == c] - sum_{k > i} U[i][k] X[k][c]) / U[i][i]
-#pragma unroll
-        for (int i = kTb - 1; i >= 0; --i) {
-          float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-#pragma unroll
-          for (int k = i + 1; k + 3 < kTb; k += 4) {
-            s0 += s_d[i][k] * xc[k];
-            s1 += s_d[i][k + 1] * xc[k + 1];
-            s2 += s_d[i][k + 2] * xc[k + 2];
-            s3 += s_d[i][k + 3] * xc[k + 3];
-          }
-#pragma unroll
-          for (int k = kTb - ((kTb - 1 - i) & 3); k < kTb; ++k) s0 += s_d[i][k] * xc[k];
-          const float sum = (s0 + s1) + (s2 + s3);
-          xc[i] = i > lane ? 0.f : ((i == lane ? 1.f : 0.f) - sum) / s_d[i][i];
-        }
-      }
-      wave_sync_lds();
-      float* dcol = &s_di[0][pc];
-#pragma unroll
-      for (int i = 0; i < kTb; ++i) dcol[i * kLd] = xc[i];
-    }
+    // the lower pass of the tile LU's factors applies the block row's
+    // interchanges first: (D^-1 P)[i][p(c)] = D^-1[i][c]
+    if (w == 0) s_pc[lane] = (LOCALP && !UPPER && lane < rows) ? sy.perm[row] - (int)r0 : lane;
     __syncthreads();
+    if (UPPER)
+      invert_tri64<true>(s_d, s_di, s_pc, w, lane);
+    else
+      invert_tri64<false>(s_d, s_di, s_pc, w, lane);
     // M = D^-1 A_bl: wave w forms rows 16w..16w+15
     if (has_jl) {
       floatx4 acc[4];
