@@ -136,8 +136,8 @@ struct Arena {
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 inline int64_t lda_for(int64_t n) { return round_up(n < 1 ? 1 : n, 64); }
 // doubles of scratch the |A|_inf kernels need
-inline int64_t rowsum_chunks(int64_t n) { return n <= 4096 ? (n + 255) / 256 : 16; }
-inline int64_t rowsum_scratch(int64_t n) { return rowsum_chunks(n) * n + 1024; }
+inline int64_t rowsum_chunks(int64_t n) { return n <= 64 * 64 ? (n + 63) / 64 : 64; }
+inline int64_t rowsum_scratch(int64_t n) { return rowsum_chunks(n) * n; }
 
 // One quadrature point as a source of the field sum: position and
 // g = w_q f[nu(q)] (zero when nu(q) is outside [0, N)); 64 bytes so that a
