@@ -231,10 +231,10 @@ __global__ __launch_bounds__(kAsmBlock) void k_assemble64(
 
 // b = [u; f_ext or 0]; with b32 != NULL also its FP32 copy; with st != NULL
 // also the body-index check (body[m] in [-1, M), else an argument error).
-__global__ void k_rhs(int64_t N, int32_t M, const double* __restrict__ u,
-                      const double* __restrict__ ft, double* __restrict__ b,
-                      float* __restrict__ b32, const int32_t* __restrict__ body, SolveState* st) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+__device__ inline void rhs_entry(int64_t i, int64_t N, int32_t M, const double* __restrict__ u,
+                                 const double* __restrict__ ft, double* __restrict__ b,
+                                 float* __restrict__ b32, const int32_t* __restrict__ body,
+                                 SolveState* st) {
   const int64_t n = 3 * N + 6 * (int64_t)M;
   if (st && i < N && (body[i] < -1 || body[i] >= M)) {
     st->nonfinite = 2;
@@ -245,6 +245,22 @@ __global__ void k_rhs(int64_t N, int32_t M, const double* __restrict__ u,
   const double v = i < 3 * N ? u[i] : (ft ? ft[i - 3 * N] : 0.0);
   b[i] = v;
   if (b32) b32[i] = (float)v;
+}
+
+constexpr int kRhsThreads = 256;
+__global__ void k_rhs(int64_t N, int32_t M, const double* __restrict__ u,
+                      const double* __restrict__ ft, double* __restrict__ b,
+                      float* __restrict__ b32, const int32_t* __restrict__ body, SolveState* st) {
+  rhs_entry(blockIdx.x * (int64_t)kRhsThreads + threadIdx.x, N, M, u, ft, b, b32, body, st);
+}
+
+__global__ void k_rhs_batch(const BatchSys* __restrict__ sys, const int64_t* __restrict__ first,
+                            int32_t s0, int32_t s1) {
+  const int64_t g = first[s0] + blockIdx.x;
+  const int32_t s = batch_find(first, s0, s1, g);
+  const BatchSys& y = sys[s];
+  rhs_entry((g - first[s]) * kRhsThreads + threadIdx.x, y.N, y.M, as_global(y.u), as_global(y.ft),
+            as_global(y.b), as_global(y.r32), as_global(y.body), as_global(y.st));
 }
 
 // Pair sum of the matrix-free product: chunk partial sums of the flow of the
@@ -264,25 +280,24 @@ __global__ void k_rhs(int64_t N, int32_t M, const double* __restrict__ u,
 // (1000 x 10,000) 21.6 -> 14.3 us, 100 filaments (4000 x 40,000) 100.8 -> 102.9 us.
 constexpr int kPairThreads = 256;
 constexpr int kPairWaves = kPairThreads / 64;
-__global__ __launch_bounds__(kPairThreads) void k_apply_pairs(
-    int64_t N, int64_t pblocks, int32_t chunks, int64_t chunk, const double* __restrict__ x,
-    const int32_t* __restrict__ seg, const int32_t* __restrict__ nus,
-    const double4* __restrict__ X64, const double* __restrict__ f, double eps2,
-    double* __restrict__ part, const int32_t* __restrict__ stop) {
-  if (stop && *stop) return;
+__device__ __forceinline__ void apply_pairs(
+    int64_t block, int64_t N, int64_t pblocks, int32_t chunks, int64_t chunk,
+    const double* __restrict__ x, const int32_t* __restrict__ seg,
+    const int32_t* __restrict__ nus, const double4* __restrict__ X64,
+    const double* __restrict__ f, double eps2, double* __restrict__ part) {
   __shared__ double red[3][kPairWaves][64];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int32_t ch;
   int64_t pb;
   if (chunks >= 8) {
-    const int64_t j = blockIdx.x >> 3;
+    const int64_t j = block >> 3;
     pb = j % pblocks;
-    ch = 8 * (int32_t)(j / pblocks) + (int32_t)(blockIdx.x & 7);
+    ch = 8 * (int32_t)(j / pblocks) + (int32_t)(block & 7);
     if (ch >= chunks) return;
   } else {
-    ch = blockIdx.x % chunks;
-    pb = blockIdx.x / chunks;
+    ch = (int32_t)(block % chunks);
+    pb = block / chunks;
   }
   const int64_t m = pb * 64 + lane;
   double px = 0.0, py = 0.0, pz = 0.0;
@@ -345,12 +360,32 @@ __global__ __launch_bounds__(kPairThreads) void k_apply_pairs(
   }
 }
 
+__global__ __launch_bounds__(kPairThreads) void k_apply_pairs(
+    int64_t N, int64_t pblocks, int32_t chunks, int64_t chunk, const double* __restrict__ x,
+    const int32_t* __restrict__ seg, const int32_t* __restrict__ nus,
+    const double4* __restrict__ X64, const double* __restrict__ f, double eps2,
+    double* __restrict__ part, const int32_t* __restrict__ stop) {
+  if (stop && *stop) return;
+  apply_pairs(blockIdx.x, N, pblocks, chunks, chunk, x, seg, nus, X64, f, eps2, part);
+}
+
+__global__ __launch_bounds__(kPairThreads) void k_apply_pairs_batch(
+    const BatchSys* __restrict__ sys, const int64_t* __restrict__ first, int32_t s0, int32_t s1,
+    int force) {
+  const int64_t g = first[s0] + blockIdx.x;
+  const int32_t s = batch_find(first, s0, s1, g);
+  const BatchSys& y = sys[s];
+  if (!force && as_global(y.st)->stop) return;
+  apply_pairs(g - first[s], y.N, y.pblocks, y.chunks, y.chunk, as_global(y.x), as_global(y.seg),
+              as_global(y.nus), as_global(y.X64), as_global(y.sol), y.eps2, as_global(y.part));
+}
+
 constexpr int kApplyThreads = 256;
 
 // Stage 2 for the 3N velocity rows: sum the chunks in a fixed order (wave w
 // takes a contiguous quarter of them with four running sums), scale,
 // subtract the rigid-body motion U + Omega x r_m of free-body points.
-__device__ inline void apply_velocity_rows(int64_t N, int32_t M, int32_t chunks,
+__device__ inline void apply_velocity_rows(int64_t block, int64_t N, int32_t M, int32_t chunks,
                                            const double* __restrict__ part, double scale,
                                            const double* __restrict__ x,
                                            const int32_t* __restrict__ body,
@@ -358,7 +393,7 @@ __device__ inline void apply_velocity_rows(int64_t N, int32_t M, int32_t chunks,
                                            const double* __restrict__ v, double* __restrict__ y) {
   __shared__ double red[kApplyThreads / 64][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t row = blockIdx.x * (int64_t)64 + lane;
+  const int64_t row = block * 64 + lane;
   const int per = (chunks + kApplyThreads / 64 - 1) / (kApplyThreads / 64);
   const int c0 = w * per, c1 = min(chunks, c0 + per);
   double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
@@ -424,18 +459,38 @@ __device__ inline void apply_body_rows(int s, int64_t N, const int32_t* __restri
 
 // Stage 2 of the product in one launch: workgroups [0, rowblocks) take the
 // velocity rows, workgroup rowblocks + s the rigid rows of body s.
+__device__ __forceinline__ void apply_stage2(
+    int64_t block, int64_t N, int32_t M, int32_t chunks, const double* __restrict__ part,
+    double scale, const double* __restrict__ x, const int32_t* __restrict__ body,
+    const double* __restrict__ Y, const double* __restrict__ W, const double* __restrict__ v,
+    double* __restrict__ y) {
+  const int64_t rowblocks = (3 * N + 63) / 64;
+  if (block >= rowblocks) {
+    apply_body_rows((int)(block - rowblocks), N, body, x, Y, W, v, y);
+    return;
+  }
+  apply_velocity_rows(block, N, M, chunks, part, scale, x, body, Y, v, y);
+}
+
 __global__ __launch_bounds__(kApplyThreads) void k_apply_stage2(
     int64_t N, int32_t M, int32_t chunks, const double* __restrict__ part, double scale,
     const double* __restrict__ x, const int32_t* __restrict__ body,
     const double* __restrict__ Y, const double* __restrict__ W, const double* __restrict__ v,
     double* __restrict__ y, const int32_t* __restrict__ stop) {
   if (stop && *stop) return;
-  const int64_t rowblocks = (3 * N + 63) / 64;
-  if ((int64_t)blockIdx.x >= rowblocks) {
-    apply_body_rows((int)(blockIdx.x - rowblocks), N, body, x, Y, W, v, y);
-    return;
-  }
-  apply_velocity_rows(N, M, chunks, part, scale, x, body, Y, v, y);
+  apply_stage2(blockIdx.x, N, M, chunks, part, scale, x, body, Y, W, v, y);
+}
+
+__global__ __launch_bounds__(kApplyThreads) void k_apply_stage2_batch(
+    const BatchSys* __restrict__ sys, const int64_t* __restrict__ first, int32_t s0, int32_t s1,
+    int force) {
+  const int64_t g = first[s0] + blockIdx.x;
+  const int32_t s = batch_find(first, s0, s1, g);
+  const BatchSys& y = sys[s];
+  if (!force && as_global(y.st)->stop) return;
+  apply_stage2(g - first[s], y.N, y.M, y.chunks, as_global(y.part), y.scale, as_global(y.x),
+               as_global(y.body), as_global(y.Y), as_global(y.W), as_global(y.sol),
+               as_global(y.Ax));
 }
 
 inline dim3 grid1(int64_t n, int b) { return dim3((unsigned)((n + b - 1) / b)); }
@@ -526,9 +581,15 @@ template hipError_t launch_assemble<double>(const nrs_problem&, const Sorted&, d
 hipError_t launch_rhs(int64_t N, int32_t M, const double* u, const double* ftext, double* b,
                       hipStream_t s, float* b32, const int32_t* body, SolveState* st) {
   const int64_t n = 3 * N + 6 * (int64_t)M;
-  hipLaunchKernelGGL(k_rhs, grid1(std::max(n, st ? N : 0), 256), dim3(256), 0, s, N, M, u, ftext,
-                     b, b32, body, st);
+  hipLaunchKernelGGL(k_rhs, grid1(std::max(n, st ? N : 0), kRhsThreads), dim3(kRhsThreads), 0, s,
+                     N, M, u, ftext, b, b32, body, st);
   return hipGetLastError();
+}
+
+hipError_t launch_rhs_batch(const BatchSet& bs, hipStream_t s) {
+  return batch_launch(bs, kBatchRhs, [&](const int64_t* first, int32_t s0, int32_t s1, unsigned g) {
+    hipLaunchKernelGGL(k_rhs_batch, dim3(g), dim3(kRhsThreads), 0, s, bs.sys, first, s0, s1);
+  });
 }
 
 // Chunks of the pair sum: 2048 workgroups (eight per CU) while the sources give
@@ -547,6 +608,11 @@ FieldPlan apply_plan(int64_t N, int64_t Q) {
   return fp;
 }
 
+// Workgroups of the pair sum: whole rounds of the eight XCDs from eight chunks on.
+static int64_t pair_blocks(int64_t pblocks, int32_t chunks) {
+  return pblocks * (chunks >= 8 ? 8 * ((chunks + 7) / 8) : chunks);
+}
+
 // Matrix-free FP64 product: the velocity rows are the flow of the force
 // densities v at the force points (chunk partial sums over the nu-sorted sources),
 // then the fixed-order chunk sum with the rigid-body motion and the balance rows
@@ -558,9 +624,8 @@ hipError_t launch_apply(const nrs_problem& pb, const Sorted& srt, const double* 
   if (N > 0) {
     const FieldPlan fp = apply_plan(N, Q);
     if (fp.chunks > chunks) return hipErrorInvalidValue;
-    const int64_t slots = fp.chunks >= 8 ? 8 * ((fp.chunks + 7) / 8) : fp.chunks;
-    hipLaunchKernelGGL(k_apply_pairs, dim3((unsigned)(fp.pblocks * slots)), dim3(kPairThreads), 0,
-                       s, N, fp.pblocks, fp.chunks, fp.chunk, pb.x, srt.seg, srt.nus, srt.X64, v,
+    hipLaunchKernelGGL(k_apply_pairs, dim3((unsigned)pair_blocks(fp.pblocks, fp.chunks)),
+                       dim3(kPairThreads), 0, s, N, fp.pblocks, fp.chunks, fp.chunk, pb.x, srt.seg, srt.nus, srt.X64, v,
                        pb.eps * pb.eps, part, stop);
     const unsigned blocks = (unsigned)((3 * N + 63) / 64 + pb.M);
     hipLaunchKernelGGL(k_apply_stage2, dim3(blocks), dim3(kApplyThreads), 0, s, N, pb.M,
@@ -568,6 +633,29 @@ hipError_t launch_apply(const nrs_problem& pb, const Sorted& srt, const double* 
                        y, stop);
   }
   return hipGetLastError();
+}
+
+// The same for every system of a batch, Ax at sol, in two launches (96 systems of orders
+// 300..6000: about 1.0 ms, as the FP64 rate of the pair sum gives).
+hipError_t launch_apply_batch(const BatchSet& bs, int force, hipStream_t s) {
+  hipError_t e =
+      batch_launch(bs, kBatchPairs, [&](const int64_t* first, int32_t s0, int32_t s1, unsigned g) {
+        hipLaunchKernelGGL(k_apply_pairs_batch, dim3(g), dim3(kPairThreads), 0, s, bs.sys, first,
+                           s0, s1, force);
+      });
+  if (e != hipSuccess) return e;
+  return batch_launch(bs, kBatchRows, [&](const int64_t* first, int32_t s0, int32_t s1, unsigned g) {
+    hipLaunchKernelGGL(k_apply_stage2_batch, dim3(g), dim3(kApplyThreads), 0, s, bs.sys, first, s0,
+                       s1, force);
+  });
+}
+
+int64_t batch_blocks_assemble(int kind, const BatchSys& y) {
+  switch (kind) {
+    case kBatchRhs: return (std::max(y.n, y.N) + kRhsThreads - 1) / kRhsThreads;
+    case kBatchPairs: return pair_blocks(y.pblocks, y.chunks);
+    default: return (3 * y.N + 63) / 64 + y.M;   // kBatchRows
+  }
 }
 
 }  // namespace nrs

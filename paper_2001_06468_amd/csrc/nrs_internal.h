@@ -136,7 +136,7 @@ struct Arena {
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 inline int64_t lda_for(int64_t n) { return round_up(n < 1 ? 1 : n, 64); }
 // doubles of scratch the |A|_inf kernels need
-inline int64_t rowsum_chunks(int64_t n) { return n <= 64 * 64 ? (n + 63) / 64 : 64; }
+__host__ __device__ inline int64_t rowsum_chunks(int64_t n) { return n <= 64 * 64 ? (n + 63) / 64 : 64; }
 inline int64_t rowsum_scratch(int64_t n) { return rowsum_chunks(n) * n; }
 
 // One quadrature point as a source of the field sum: position and
@@ -205,6 +205,81 @@ struct SolveBuffers {
 };
 
 size_t solve_workspace_bytes(int64_t N, int64_t Q, int32_t M, int32_t method);
+
+// One system of a batch, as the kernels that run over all systems of a batch read it.
+struct BatchSys {
+  int64_t N, Q, n, lda, nsync, ndone, pblocks, chunk;
+  int32_t chunks, M;
+  double eps2, scale;   // eps^2, 1 / (8 pi mu)
+  const double *x, *X, *w, *Y, *u, *ft;
+  const int32_t *nu, *body;
+  int32_t *seg, *perm, *nus, *tsync, *done;
+  double4* X64;
+  float4 *X32hi, *X32lo;
+  double *W, *b, *sol, *r, *Ax, *part, *red;
+  float *A, *r32, *d32;
+  SolveState* st;
+};
+
+// Launches over all systems of a batch.  Workgroup g of a launch belongs to the system s
+// with first[s] <= g < first[s + 1]; within it the workgroup does what workgroup
+// g - first[s] of the single system's launch does, by the same code, so results are those of the
+// single solve bit for bit.
+enum { kBatchBegin, kBatchCsr, kBatchRhs, kBatchNorm, kBatchNormMax, kBatchPairs, kBatchRows, kBatchKinds };
+struct BatchSet {
+  int32_t B;
+  const BatchSys* sys;    // device
+  const int64_t* first;   // device, [kBatchKinds][B + 1]
+  const int64_t* host;    // the same on the host
+};
+// Workgroups of system s's share of a launch (also the host's count of them).
+int64_t batch_blocks_assemble(int kind, const BatchSys& y);
+int64_t batch_blocks_refine(int kind, const BatchSys& y);
+int64_t batch_blocks_points(const BatchSys& y);   // 0: past the one-launch layout's sizes
+// A grid holds fewer than 2^32 threads: a launch takes as many systems as fit in this many
+// workgroups (of at most 1024 threads), and the rest go into further launches.
+constexpr int64_t kBatchMaxBlocks = 1 << 21;
+template <class F>
+hipError_t batch_launch(const BatchSet& bs, int kind, F launch) {
+  const int64_t* f = bs.host + kind * (int64_t)(bs.B + 1);
+  for (int32_t s0 = 0, s1; s0 < bs.B; s0 = s1) {
+    s1 = s0 + 1;
+    while (s1 < bs.B && f[s1 + 1] - f[s0] <= kBatchMaxBlocks) ++s1;
+    if (f[s1] > f[s0])
+      launch(bs.first + kind * (int64_t)(bs.B + 1), s0, s1, (unsigned)(f[s1] - f[s0]));
+  }
+  return hipGetLastError();
+}
+// System of workgroup g among systems [s0, s1).
+__device__ inline int32_t batch_find(const int64_t* __restrict__ first, int32_t s0, int32_t s1,
+                                     int64_t g) {
+  while (s1 - s0 > 1) {
+    const int32_t mid = (s0 + s1) >> 1;
+    if (first[mid] <= g)
+      s0 = mid;
+    else
+      s1 = mid;
+  }
+  return s0;
+}
+// A pointer of a descriptor in memory, read as one to global memory (scalar and global
+// loads through it instead of flat ones).
+template <class T>
+__device__ inline T* as_global(T* const& p) {
+  return (T*)*reinterpret_cast<__attribute__((address_space(1))) T* const*>(&p);
+}
+
+hipError_t launch_begin_batch(const BatchSet& bs, int32_t method, hipStream_t s);
+hipError_t launch_csr_batch(const BatchSet& bs, hipStream_t s);
+hipError_t launch_rhs_batch(const BatchSet& bs, hipStream_t s);
+hipError_t launch_anorm_batch(const BatchSet& bs, hipStream_t s);
+// force: also for systems whose refinement has ended
+hipError_t launch_apply_batch(const BatchSet& bs, int force, hipStream_t s);
+// last: the FP64 residual of the report instead of the next correction's right-hand side
+hipError_t launch_residual_batch(const BatchSet& bs, int last, hipStream_t s);
+hipError_t launch_update_batch(const BatchSet& bs, double tol, int32_t first, hipStream_t s);
+// states [B] = the systems' status records
+hipError_t launch_states_batch(const BatchSet& bs, SolveState* states, hipStream_t s);
 // with64 = false leaves out the FP64 matrix and the tile LU's row-tile
 // hand-over area (batched FP32 solves)
 bool carve_solve(Arena& ar, int64_t N, int64_t Q, int32_t M, int32_t method, SolveBuffers& sb,

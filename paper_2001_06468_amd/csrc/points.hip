@@ -407,8 +407,8 @@ constexpr int kSegCap = 512;
 constexpr int kSegBatch = 8;
 constexpr int kSegW = 64;
 
-__global__ __launch_bounds__(kSegWaves * 64) void k_csr_segments(
-    int64_t N, int64_t Q, const int32_t* __restrict__ nu, const double* __restrict__ X,
+__device__ __forceinline__ void csr_segments(
+    int32_t block, int64_t N, int64_t Q, const int32_t* __restrict__ nu, const double* __restrict__ X,
     const double* __restrict__ w, int32_t* __restrict__ seg, int32_t* __restrict__ perm,
     int32_t* __restrict__ nus, double4* __restrict__ X64, float4* __restrict__ X32hi,
     float4* __restrict__ X32lo, double* __restrict__ W, SolveState* st) {
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kSegWaves * 64) void k_csr_segments(
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint64_t lower = (1ull << lane) - 1;
-  const int32_t n0 = (int32_t)blockIdx.x * kSegPts;
+  const int32_t n0 = block * kSegPts;
   const int32_t n1 = (int32_t)min<int64_t>(N, n0 + kSegPts);
   const int32_t per = ((int32_t)Q + kSegWaves * 64 - 1) / (kSegWaves * 64) * 64;
   const int32_t qa = min((int32_t)Q, wv * per), qb = min((int32_t)Q, qa + per);
@@ -467,7 +467,7 @@ __global__ __launch_bounds__(kSegWaves * 64) void k_csr_segments(
     below[wv] = lo;
     len[wv] = found;
   }
-  if (blockIdx.x == 0 && st && bad) {
+  if (block == 0 && st && bad) {
     st->nonfinite = 2;
     st->failed = 1;
     st->stop = 1;
@@ -546,6 +546,24 @@ __global__ __launch_bounds__(kSegWaves * 64) void k_csr_segments(
   }
 }
 
+__global__ __launch_bounds__(kSegWaves * 64) void k_csr_segments(
+    int64_t N, int64_t Q, const int32_t* __restrict__ nu, const double* __restrict__ X,
+    const double* __restrict__ w, int32_t* __restrict__ seg, int32_t* __restrict__ perm,
+    int32_t* __restrict__ nus, double4* __restrict__ X64, float4* __restrict__ X32hi,
+    float4* __restrict__ X32lo, double* __restrict__ W, SolveState* st) {
+  csr_segments((int32_t)blockIdx.x, N, Q, nu, X, w, seg, perm, nus, X64, X32hi, X32lo, W, st);
+}
+
+__global__ __launch_bounds__(kSegWaves * 64) void k_csr_segments_batch(
+    const BatchSys* __restrict__ sys, const int64_t* __restrict__ first, int32_t s0, int32_t s1) {
+  const int64_t g = first[s0] + blockIdx.x;
+  const int32_t s = batch_find(first, s0, s1, g);
+  const BatchSys& y = sys[s];
+  csr_segments((int32_t)(g - first[s]), y.N, y.Q, as_global(y.nu), as_global(y.X), as_global(y.w),
+               as_global(y.seg), as_global(y.perm), as_global(y.nus), as_global(y.X64),
+               as_global(y.X32hi), as_global(y.X32lo), as_global(y.W), as_global(y.st));
+}
+
 inline dim3 grid1(int64_t n, int b) { return dim3((unsigned)((n + b - 1) / b)); }
 
 }  // namespace
@@ -607,6 +625,17 @@ hipError_t launch_build_csr(int64_t N, int64_t Q, const double* X, const double*
                      dim3(kFinishWaves * 64), 0, s, N, Q, srt.seg, srt.perm, X, w, srt.nus, srt.X64,
                      srt.X32hi, srt.X32lo, srt.W);
   return hipGetLastError();
+}
+
+int64_t batch_blocks_points(const BatchSys& y) {
+  return y.N <= kCsrSmallN && y.Q <= kCsrSmallQ ? (y.N + kSegPts - 1) / kSegPts : 0;
+}
+
+hipError_t launch_csr_batch(const BatchSet& bs, hipStream_t s) {
+  return batch_launch(bs, kBatchCsr, [&](const int64_t* first, int32_t s0, int32_t s1, unsigned g) {
+    hipLaunchKernelGGL(k_csr_segments_batch, dim3(g), dim3(kSegWaves * 64), 0, s, bs.sys, first, s0,
+                       s1);
+  });
 }
 
 }  // namespace nrs

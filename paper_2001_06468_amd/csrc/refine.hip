@@ -1,6 +1,8 @@
 // Mixed-precision iterative refinement (FP32 factors, FP64 residual and
 // update), status bookkeeping, and the RK4 time-stepping kernels (Sec. 4:
 // Y' = F(Y, t) with Y = [X0; B]).
+#include <algorithm>
+
 #include "nrs_internal.h"
 
 namespace nrs {
@@ -37,9 +39,9 @@ __global__ void k_state_init(SolveState* st, int32_t method) {
 
 // The start of a solve in one launch: the status record, and the
 // triangular-solve and tile-LU synchronisation words zeroed.
-__global__ void k_solve_begin(SolveState* st, int32_t method, int32_t* __restrict__ a, int64_t na,
-                              int32_t* __restrict__ b, int64_t nb) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+__device__ inline void solve_begin_entry(int64_t i, SolveState* st, int32_t method,
+                                         int32_t* __restrict__ a, int64_t na,
+                                         int32_t* __restrict__ b, int64_t nb) {
   if (i == 0) {
     SolveState z = {};
     z.method_used = method;
@@ -49,21 +51,39 @@ __global__ void k_solve_begin(SolveState* st, int32_t method, int32_t* __restric
   if (i < nb) b[i] = 0;
 }
 
+constexpr int kBeginThreads = 256;
+__global__ void k_solve_begin(SolveState* st, int32_t method, int32_t* __restrict__ a, int64_t na,
+                              int32_t* __restrict__ b, int64_t nb) {
+  solve_begin_entry(blockIdx.x * (int64_t)kBeginThreads + threadIdx.x, st, method, a, na, b, nb);
+}
+
+__global__ void k_solve_begin_batch(const BatchSys* __restrict__ sys,
+                                    const int64_t* __restrict__ first, int32_t s0, int32_t s1,
+                                    int32_t method) {
+  const int64_t g = first[s0] + blockIdx.x;
+  const int32_t s = batch_find(first, s0, s1, g);
+  const BatchSys& y = sys[s];
+  solve_begin_entry((g - first[s]) * kBeginThreads + threadIdx.x, as_global(y.st), method,
+                    as_global(y.tsync), y.nsync, as_global(y.done), y.ndone);
+}
+
 // |A|_inf = max_i sum_j |a_ij| (column-major, 16-byte aligned columns).  Stage 1: a
 // thread sums 16 bytes of rows over its workgroup's columns, four columns of loads in
 // flight, into part[chunk][row]; stage 2: per-row sum of the chunks in order and the
 // maximum over the rows, combined across workgroups as an integer maximum of its
 // bits (non-negative, never a NaN) in st->anorm, zeroed by stage 1.  Bound by HBM: 635 MB (FP32, n = 12,600) 400 us at one row and one load per
 // thread, 165 us (3.85 TB/s) so.
+constexpr int kSumThreads = 64, kMaxThreads = 256;
 template <class T>
-__global__ void k_rowsum(int64_t n, const T* __restrict__ A, int64_t lda, int64_t cw,
-                         double* __restrict__ part, SolveState* st) {
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) st->anorm = 0.0;
+__device__ __forceinline__ void rowsum(int64_t bx, int64_t by, int64_t n,
+                                       const T* __restrict__ A, int64_t lda, int64_t cw,
+                                       double* __restrict__ part, SolveState* st) {
+  if (bx == 0 && by == 0 && threadIdx.x == 0) st->anorm = 0.0;
   constexpr int V = 16 / (int)sizeof(T);
   typedef T vec __attribute__((ext_vector_type(V)));
-  const int64_t i = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) * V;
+  const int64_t i = (bx * kSumThreads + threadIdx.x) * V;
   if (i >= n) return;
-  const int64_t j0 = blockIdx.y * cw, j1 = min<int64_t>(n, j0 + cw);
+  const int64_t j0 = by * cw, j1 = min<int64_t>(n, j0 + cw);
   double s[V];
 #pragma unroll
   for (int e = 0; e < V; ++e) s[e] = 0.0;
@@ -87,13 +107,30 @@ __global__ void k_rowsum(int64_t n, const T* __restrict__ A, int64_t lda, int64_
   }
 #pragma unroll
   for (int e = 0; e < V; ++e)
-    if (i + e < n) part[blockIdx.y * n + i + e] = s[e];
+    if (i + e < n) part[by * n + i + e] = s[e];
 }
 
-__global__ void k_rowsum_max(int64_t n, int64_t chunks, const double* __restrict__ part,
-                             SolveState* st) {
+template <class T>
+__global__ void k_rowsum(int64_t n, const T* __restrict__ A, int64_t lda, int64_t cw,
+                         double* __restrict__ part, SolveState* st) {
+  rowsum<T>(blockIdx.x, blockIdx.y, n, A, lda, cw, part, st);
+}
+
+__global__ void k_rowsum_batch(const BatchSys* __restrict__ sys, const int64_t* __restrict__ first,
+                               int32_t s0, int32_t s1) {
+  const int64_t g = first[s0] + blockIdx.x;
+  const int32_t s = batch_find(first, s0, s1, g);
+  const BatchSys& y = sys[s];
+  const int64_t gx = (y.n + 4 * kSumThreads - 1) / (4 * kSumThreads), l = g - first[s];
+  const int64_t chunks = rowsum_chunks(y.n);
+  rowsum<float>(l % gx, l / gx, y.n, as_global(y.A), y.lda, (y.n + chunks - 1) / chunks,
+                as_global(y.red), as_global(y.st));
+}
+
+__device__ __forceinline__ void rowsum_max(int64_t block, int64_t n, int64_t chunks,
+                                           const double* __restrict__ part, SolveState* st) {
   __shared__ double sh[64];
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t i = block * kMaxThreads + threadIdx.x;
   double s = 0.0;
   if (i < n)
 #pragma unroll 8
@@ -102,6 +139,19 @@ __global__ void k_rowsum_max(int64_t n, int64_t chunks, const double* __restrict
   if (threadIdx.x == 0)
     atomicMax(reinterpret_cast<unsigned long long*>(&st->anorm),
               (unsigned long long)__double_as_longlong(m));
+}
+
+__global__ void k_rowsum_max(int64_t n, int64_t chunks, const double* __restrict__ part,
+                             SolveState* st) {
+  rowsum_max(blockIdx.x, n, chunks, part, st);
+}
+
+__global__ void k_rowsum_max_batch(const BatchSys* __restrict__ sys,
+                                   const int64_t* __restrict__ first, int32_t s0, int32_t s1) {
+  const int64_t g = first[s0] + blockIdx.x;
+  const int32_t s = batch_find(first, s0, s1, g);
+  const BatchSys& y = sys[s];
+  rowsum_max(g - first[s], y.n, rowsum_chunks(y.n), as_global(y.red), as_global(y.st));
 }
 
 // Equilibration of the FP32 matrix (row, then column scaling by powers of
@@ -163,15 +213,12 @@ __global__ void k_convert_scaled(int64_t n, const double* __restrict__ a,
 
 // r = b - A x (FP64), r in the correction precision; backward error from
 // |r|, |x| (x is the solution the residual was taken at) and |b|.
-__global__ __launch_bounds__(kRedThreads) void k_ir_residual(int64_t n,
-                                                             const double* __restrict__ b,
-                                                             const double* __restrict__ Ax,
-                                                             const double* __restrict__ x,
-                                                             double* __restrict__ r,
-                                                             float* __restrict__ r32,
-                                                             double* __restrict__ r64,
-                                                             SolveState* st, int force,
-                                                             const float* __restrict__ eqr) {
+__device__ __forceinline__ void ir_residual(int64_t n, const double* __restrict__ b,
+                                            const double* __restrict__ Ax,
+                                            const double* __restrict__ x, double* __restrict__ r,
+                                            float* __restrict__ r32, double* __restrict__ r64,
+                                            SolveState* st, int force,
+                                            const float* __restrict__ eqr) {
   __shared__ double sh[64];
   if (!force && (st->converged || st->failed)) return;
   double rmax = 0.0, bmax = 0.0, xmax = 0.0;
@@ -201,14 +248,27 @@ __global__ __launch_bounds__(kRedThreads) void k_ir_residual(int64_t n,
   }
 }
 
+__global__ __launch_bounds__(kRedThreads) void k_ir_residual(
+    int64_t n, const double* __restrict__ b, const double* __restrict__ Ax,
+    const double* __restrict__ x, double* __restrict__ r, float* __restrict__ r32,
+    double* __restrict__ r64, SolveState* st, int force, const float* __restrict__ eqr) {
+  ir_residual(n, b, Ax, x, r, r32, r64, st, force, eqr);
+}
+
+__global__ __launch_bounds__(kRedThreads) void k_ir_residual_batch(
+    const BatchSys* __restrict__ sys, int last) {
+  const BatchSys& y = sys[blockIdx.x];
+  ir_residual(y.n, as_global(y.b), as_global(y.Ax), as_global(y.sol),
+              last ? as_global(y.r) : nullptr, last ? nullptr : as_global(y.r32), nullptr,
+              as_global(y.st), last, nullptr);
+}
+
 // x += d; convergence when |d|_inf <= tol |x|_inf or when the predicted next
 // correction is (see below); failure when the correction stops contracting
 // or turns non-finite.
-template <class T>
-__global__ __launch_bounds__(kRedThreads) void k_ir_update(int64_t n, double* __restrict__ x,
-                                                           const T* __restrict__ d, double tol,
-                                                           int32_t first, SolveState* st,
-                                                           const float* __restrict__ eqc) {
+__device__ __forceinline__ void ir_update(int64_t n, double* __restrict__ x,
+                                          const float* __restrict__ d, double tol, int32_t first,
+                                          SolveState* st, const float* __restrict__ eqc) {
   __shared__ double sh[64];
   if (st->converged || st->failed) return;
   double dmax = 0.0, xmax = 0.0;
@@ -251,6 +311,24 @@ __global__ __launch_bounds__(kRedThreads) void k_ir_update(int64_t n, double* __
     st->corr = c;
     st->stop = st->converged || st->failed;
   }
+}
+
+__global__ __launch_bounds__(kRedThreads) void k_ir_update(int64_t n, double* __restrict__ x,
+                                                           const float* __restrict__ d, double tol,
+                                                           int32_t first, SolveState* st,
+                                                           const float* __restrict__ eqc) {
+  ir_update(n, x, d, tol, first, st, eqc);
+}
+
+__global__ __launch_bounds__(kRedThreads) void k_ir_update_batch(const BatchSys* __restrict__ sys,
+                                                                 double tol, int32_t first) {
+  const BatchSys& y = sys[blockIdx.x];
+  ir_update(y.n, as_global(y.sol), as_global(y.d32), tol, first, as_global(y.st), nullptr);
+}
+
+__global__ void k_states_batch(int32_t B, const BatchSys* __restrict__ sys, SolveState* states) {
+  const int32_t s = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (s < B) states[s] = *sys[s].st;
 }
 
 template <class T>
@@ -373,9 +451,10 @@ static hipError_t anorm(int64_t n, const T* A, int64_t lda, SolveState* st, doub
   const int64_t chunks = rowsum_chunks(n);
   const int64_t cw = (n + chunks - 1) / chunks;
   constexpr int V = 16 / (int)sizeof(T);
-  hipLaunchKernelGGL(k_rowsum<T>, dim3((unsigned)((n + 64 * V - 1) / (64 * V)), (unsigned)chunks),
-                     dim3(64), 0, s, n, A, lda, cw, scratch, st);
-  hipLaunchKernelGGL(k_rowsum_max, grid1(n, 256), dim3(256), 0, s, n, chunks, scratch, st);
+  hipLaunchKernelGGL(k_rowsum<T>, dim3((unsigned)((n + kSumThreads * V - 1) / (kSumThreads * V)),
+                                       (unsigned)chunks),
+                     dim3(kSumThreads), 0, s, n, A, lda, cw, scratch, st);
+  hipLaunchKernelGGL(k_rowsum_max, grid1(n, kMaxThreads), dim3(kMaxThreads), 0, s, n, chunks, scratch, st);
   return hipGetLastError();
 }
 
@@ -399,7 +478,7 @@ hipError_t launch_ir_residual2(int64_t n, const double* b, const double* Ax, con
 
 hipError_t launch_ir_update32(int64_t n, double* x, const float* d, double tol, int32_t first,
                               SolveState* st, hipStream_t s, const float* eqc) {
-  hipLaunchKernelGGL(k_ir_update<float>, dim3(1), dim3(kRedThreads), 0, s, n, x, d, tol, first,
+  hipLaunchKernelGGL(k_ir_update, dim3(1), dim3(kRedThreads), 0, s, n, x, d, tol, first,
                      st, eqc);
   return hipGetLastError();
 }
@@ -491,7 +570,7 @@ hipError_t launch_rk_combine(int32_t M, double* Y, const double* K1, const doubl
 hipError_t launch_solve_begin(SolveState* st, int32_t method, int32_t* a, int64_t na, int32_t* b,
                               int64_t nb, hipStream_t s) {
   const int64_t m = std::max<int64_t>(1, std::max(na, nb));
-  hipLaunchKernelGGL(k_solve_begin, grid1(m, 256), dim3(256), 0, s, st, method, a, na, b, nb);
+  hipLaunchKernelGGL(k_solve_begin, grid1(m, kBeginThreads), dim3(kBeginThreads), 0, s, st, method, a, na, b, nb);
   return hipGetLastError();
 }
 
@@ -507,6 +586,53 @@ hipError_t launch_stage_end(SolveState* total, const SolveState* stage, int32_t 
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_stage_end, dim3(1), dim3(256), 0, s, total, stage, M, N, Ys, sol, K, Y, a);
+  return hipGetLastError();
+}
+
+int64_t batch_blocks_refine(int kind, const BatchSys& y) {
+  const auto up = [](int64_t v, int64_t m) { return (v + m - 1) / m; };
+  switch (kind) {
+    case kBatchBegin:
+      return up(std::max<int64_t>(1, std::max(y.nsync, y.ndone)), kBeginThreads);
+    case kBatchNorm: return up(y.n, 4 * kSumThreads) * rowsum_chunks(y.n);
+    default: return up(y.n, kMaxThreads);   // kBatchNormMax
+  }
+}
+
+hipError_t launch_begin_batch(const BatchSet& bs, int32_t method, hipStream_t s) {
+  return batch_launch(bs, kBatchBegin, [&](const int64_t* first, int32_t s0, int32_t s1, unsigned g) {
+    hipLaunchKernelGGL(k_solve_begin_batch, dim3(g), dim3(kBeginThreads), 0, s, bs.sys, first, s0,
+                       s1, method);
+  });
+}
+
+hipError_t launch_anorm_batch(const BatchSet& bs, hipStream_t s) {
+  hipError_t e =
+      batch_launch(bs, kBatchNorm, [&](const int64_t* first, int32_t s0, int32_t s1, unsigned g) {
+        hipLaunchKernelGGL(k_rowsum_batch, dim3(g), dim3(kSumThreads), 0, s, bs.sys, first, s0, s1);
+      });
+  if (e != hipSuccess) return e;
+  return batch_launch(
+      bs, kBatchNormMax, [&](const int64_t* first, int32_t s0, int32_t s1, unsigned g) {
+        hipLaunchKernelGGL(k_rowsum_max_batch, dim3(g), dim3(kMaxThreads), 0, s, bs.sys, first, s0,
+                           s1);
+      });
+}
+
+hipError_t launch_residual_batch(const BatchSet& bs, int last, hipStream_t s) {
+  hipLaunchKernelGGL(k_ir_residual_batch, dim3((unsigned)bs.B), dim3(kRedThreads), 0, s, bs.sys,
+                     last);
+  return hipGetLastError();
+}
+
+hipError_t launch_update_batch(const BatchSet& bs, double tol, int32_t first, hipStream_t s) {
+  hipLaunchKernelGGL(k_ir_update_batch, dim3((unsigned)bs.B), dim3(kRedThreads), 0, s, bs.sys, tol,
+                     first);
+  return hipGetLastError();
+}
+
+hipError_t launch_states_batch(const BatchSet& bs, SolveState* states, hipStream_t s) {
+  hipLaunchKernelGGL(k_states_batch, grid1(bs.B, 64), dim3(64), 0, s, bs.B, bs.sys, states);
   return hipGetLastError();
 }
 
