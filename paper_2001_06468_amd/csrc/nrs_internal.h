@@ -449,8 +449,8 @@ struct GmresArgs {
   const double* AT;   // row-major operator, row r at AT + r * ld
   const double* b;
   double* x;
-  double* V;          // [n][kGmresLd]
-  double* Z = nullptr;  // [n][kGmresLd] preconditioned basis (flexible GMRES), else NULL
+  double* V;          // [n][kGmresLd] (one-workgroup kernels: [kGmresLd][n])
+  double* Z = nullptr;  // the same, preconditioned basis (flexible GMRES), else NULL
   double* w0;
   double* w1;
   double* part;       // [gmres_blocks(n)][kGmresLd]

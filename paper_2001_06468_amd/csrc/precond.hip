@@ -313,14 +313,15 @@ __global__ void k_prec_begin(GmresArgs a, double* __restrict__ zv) {
 }
 
 // Second half: every body's rows of z_k = K_b v_k (one workgroup per body).
-// ROT: K_b is body-frame, applied as R_b K_b R_b^T with R_b from Y.
+// ROT: K_b is body-frame, applied as R_b K_b R_b^T with R_b from Y.  Element (r, c) of
+// Z is at zr r + zc c.
 template <bool ROT>
 __global__ __launch_bounds__(kPrecThreads) void k_prec_block(GmresArgs a, int64_t N,
                                                              const int32_t* __restrict__ off,
                                                              int32_t nb_lim, int32_t nb_model,
                                                              const double* __restrict__ Y,
                                                              const double* __restrict__ blocks,
-                                                             int64_t stride,
+                                                             int64_t stride, int64_t zr, int64_t zc,
                                                              double* __restrict__ zv) {
   __shared__ double vb[kBlockMax];
   __shared__ double part[kPrecThreads / 128][kBlockMax];
@@ -374,42 +375,93 @@ __global__ __launch_bounds__(kPrecThreads) void k_prec_block(GmresArgs a, int64_
   }
   for (int r = tid; r < nb; r += kPrecThreads) {
     const int64_t gr = block_row(r, nbp, N, lo, b);
-    a.Z[gr * kGmresLd + k] = vb[r];
+    a.Z[gr * zr + k * zc] = vb[r];
     zv[gr] = vb[r];
   }
 }
 
 // ---- one-workgroup flexible GMRES for n <= kGmresSmallN: thread t owns rows
 // t, t + 1024, ... (at most kRows) in registers; sums over rows are reduced
-// within the workgroup in a fixed order (deterministic). ----
+// within the workgroup in a fixed order (deterministic).  V and Z are held column by
+// column here (element (r, c) at c n + r), so that a wave's rows are 512 consecutive
+// bytes: with a row's 64 entries together each load touched 64 cache lines, and
+// these took most of an Arnoldi step (n = 3150: 16.0 us, 14.7 us the end of a cycle;
+// 6.7 and 5.5 us so, with the sums below). ----
 constexpr int kOne = 1024;
 // rows per thread: 4 or 8 (n <= 4096, kGmresSmallN), so that small systems
 // hold only the registers they use
 inline int rows_for(int64_t n) { return n <= 4 * kOne ? 4 : 8; }
 
-__device__ inline double wsum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+template <int CTRL>
+__device__ inline double dpp64(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+// {a, b} -> {a.lanes 0-31, b.lanes 0-31} + {a.lanes 32-63, b.lanes 32-63} (W = 32),
+// the same by rows of 16 lanes (W = 16).
+template <int W>
+__device__ inline double fold(double a, double b) {
+  typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+  uint2v lo, hi;
+  if constexpr (W == 32) {
+    lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  } else {
+    lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  }
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// Sum over each row of 16 lanes, in every lane of it.
+__device__ inline double row_sum(double v) {
+  v += dpp64<0xB1>(v);    // quad_perm 1 0 3 2
+  v += dpp64<0x4E>(v);    // quad_perm 2 3 0 1
+  v += dpp64<0x141>(v);   // row_half_mirror
+  return v + dpp64<0x128>(v);   // row_ror 8
 }
 
-// out[c] = sum over the workgroup of v[c] (c < CNT); every thread calls it.
-template <int CNT>
-__device__ inline void group_sum(double (&v)[CNT], double* __restrict__ s_part,
-                                 double* __restrict__ out) {
+// out = sum over the workgroup of v, in every thread; one barrier.  part [16] must not be
+// the buffer of the sum before (a slow wave may still read it).
+__device__ inline double group_sum(double v, double* __restrict__ part) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  v = row_sum(v);
+  v = fold<16>(v, v);
+  v = fold<32>(v, v);
+  if (lane == 0) part[w] = v;
+  __syncthreads();
+  return row_sum(part[lane & 15]);
+}
+
+// out[c] = sum over the workgroup of v[c] (c < 8), in every thread; also into h[0..8) for
+// reads after the next barrier (wave 0's lanes).  Each step of a wave's sum halves the
+// values a lane carries instead of summing each over all lanes: 34 instructions
+// instead of 48 shuffles.  One barrier; part [128] as above.
+__device__ inline void group_sum8(const double (&v)[8], double* __restrict__ part,
+                                  double (&out)[8], double* __restrict__ h) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double a[4], b[2];
 #pragma unroll
-  for (int c = 0; c < CNT; ++c) {
-    const double t = wsum(v[c]);
-    if (lane == 0) s_part[w * CNT + c] = t;
-  }
+  for (int c = 0; c < 4; ++c) a[c] = fold<32>(v[c], v[c + 4]);
+#pragma unroll
+  for (int c = 0; c < 2; ++c) b[c] = fold<16>(a[c], a[c + 2]);
+  const bool up = lane & 8;
+  double t = (up ? b[1] : b[0]) + dpp64<0x128>(up ? b[0] : b[1]);   // row_ror 8
+  t += dpp64<0x141>(t);
+  t += dpp64<0xB1>(t);
+  t += dpp64<0x4E>(t);
+  if ((lane & 7) == 0)   // this lane group's column
+    part[w * 8 + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1)] = t;
   __syncthreads();
-  if ((int)threadIdx.x < CNT) {
-    double t = 0.0;
-    for (int q = 0; q < kOne / 64; ++q) t += s_part[q * CNT + threadIdx.x];
-    out[threadIdx.x] = t;
-  }
-  __syncthreads();
+  t = part[lane] + part[lane + 64];   // column lane & 7, sixteen waves
+  t += dpp64<0x128>(t);
+  t = fold<16>(t, t);
+  t = fold<32>(t, t);
+  if (threadIdx.x < 8) h[threadIdx.x] = t;
+#pragma unroll
+  for (int c = 0; c < 8; ++c)
+    out[c] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(t), c),
+                              __builtin_amdgcn_readlane(__double2loint(t), c));
 }
 
 // Next basis vector v = w / nrm into V[:, col], Z[:, col] and zv.
@@ -421,8 +473,8 @@ __device__ inline void store_basis(const GmresArgs& a, int col, const double (&w
     const int64_t r = threadIdx.x + (int64_t)j * kOne;
     if (r < a.n) {
       const double v = wr[j] * scale;
-      a.V[r * kGmresLd + col] = v;
-      a.Z[r * kGmresLd + col] = v;
+      a.V[(int64_t)col * a.n + r] = v;
+      a.Z[(int64_t)col * a.n + r] = v;
       zv[r] = v;
     }
   }
@@ -437,8 +489,7 @@ __global__ __launch_bounds__(kOne) void k_bg_residual(GmresArgs a, const double*
   GmresState* st = a.st;
   if (st->done | st->fail) return;
   if (only_if_stopped && !st->stop) return;
-  __shared__ double s_part[(kOne / 64) * 2];
-  __shared__ double s_r[2];
+  __shared__ double s_part[2][kOne / 64];
   __shared__ double s_scale;
   __shared__ int s_new;
   __shared__ double s_bt[2];   // |b| (negative before the first residual), tol
@@ -459,12 +510,12 @@ __global__ __launch_bounds__(kOne) void k_bg_residual(GmresArgs a, const double*
       acc[1] = fma(br, br, acc[1]);
     }
   }
-  group_sum<2>(acc, s_part, s_r);
+  const double rsum = group_sum(acc[0], s_part[0]), bsum = group_sum(acc[1], s_part[1]);
   if (threadIdx.x == 0) {
-    const double beta = sqrt(s_r[0]);
+    const double beta = sqrt(rsum);
     double bnorm = s_bt[0];
     if (bnorm < 0.0) {
-      bnorm = sqrt(s_r[1]);
+      bnorm = sqrt(bsum);
       st->bnorm = bnorm;
     }
     st->beta = beta;
@@ -493,22 +544,20 @@ __global__ __launch_bounds__(kOne) void k_bg_residual(GmresArgs a, const double*
 
 // Arnoldi step k on w = A z_k (CGS2): h1 = V^T w, w -= V h1, h2 = V^T w,
 // w -= V h2, then the Givens rotations and stop rules; v_{k+1} = w / |w|.
+// What bounds it: one compute unit's latency: a burst of loads, three sums over the
+// workgroup, then thread 0's rotations beside the other waves' stores.
 template <int kRows>
 __global__ __launch_bounds__(kOne) void k_bg_orth(GmresArgs a, const double* __restrict__ Aw,
                                                   double* __restrict__ zv) {
   GmresState* st = a.st;
   if (st->halt) return;
   const int k = st->k;
-  constexpr int kDotW = 4;   // basis columns per pass over the rows (past the cached ones)
-  __shared__ double s_part[(kOne / 64) * 8];
-  __shared__ double s_h[2][kGmresLd];
-  __shared__ double s_n[1];
-  __shared__ double s_scale;
-  __shared__ int s_next;
+  __shared__ double s_part[2][(kOne / 64) * 8];
+  __shared__ double s_h[2][kGmresLd + 8];
   // the Givens state, staged in LDS by one round of parallel loads issued
   // before the passes over the rows (thread 0's rotations then read no
   // global memory)
-  __shared__ double s_cs[kGmresLd], s_sn[kGmresLd], s_hk[kGmresLd + 1];
+  __shared__ double s_cs[kGmresLd], s_sn[kGmresLd];
   __shared__ double s_sc[3];   // g[k], tol, |b|
   __shared__ int s_si[3];      // m, iterations, max_iter
   if (threadIdx.x < 64) {
@@ -528,7 +577,7 @@ __global__ __launch_bounds__(kOne) void k_bg_orth(GmresArgs a, const double* __r
   }
   // w and the first kVC basis columns of every row in one burst of loads,
   // kept in registers for both Gram-Schmidt passes
-  constexpr int kVC = kRows == 4 ? 6 : 3;
+  constexpr int kVC = kRows == 4 ? 8 : 4;
   double wr[kRows];
   double vc[kRows][kVC];
 #pragma unroll
@@ -536,76 +585,79 @@ __global__ __launch_bounds__(kOne) void k_bg_orth(GmresArgs a, const double* __r
     const int64_t r = threadIdx.x + (int64_t)j * kOne;
     wr[j] = r < a.n ? Aw[r] : 0.0;
 #pragma unroll
-    for (int c = 0; c < kVC; ++c) vc[j][c] = (r < a.n && c <= k) ? a.V[r * kGmresLd + c] : 0.0;
+    for (int c = 0; c < kVC; ++c) vc[j][c] = (r < a.n && c <= k) ? a.V[c * a.n + r] : 0.0;
   }
+  int buf = 0;
   for (int pass = 0; pass < 2; ++pass) {
     double* h = s_h[pass];
-    {
-      double acc[kVC];
+    double acc[8], hc[8];
 #pragma unroll
-      for (int c = 0; c < kVC; ++c) {
-        acc[c] = 0.0;
+    for (int c = 0; c < 8; ++c) {
+      acc[c] = 0.0;
+      if (c < kVC) {
 #pragma unroll
-        for (int j = 0; j < kRows; ++j) acc[c] = fma(vc[j][c], wr[j], acc[c]);
+        for (int j = 0; j < kRows; ++j) acc[c] = fma(vc[j][c < kVC ? c : 0], wr[j], acc[c]);
       }
-      group_sum<kVC>(acc, s_part, h);   // zero for columns past k
     }
-    for (int i0 = kVC; i0 <= k; i0 += kDotW) {
-      double acc[kDotW];
+    group_sum8(acc, s_part[buf], hc, h);   // zero for columns past k
+    buf ^= 1;
+    for (int i0 = kVC; i0 <= k; i0 += 8) {
+      double o[8];
 #pragma unroll
-      for (int c = 0; c < kDotW; ++c) acc[c] = 0.0;
+      for (int c = 0; c < 8; ++c) {
+        acc[c] = 0.0;
+        if (i0 + c <= k) {
 #pragma unroll
-      for (int j = 0; j < kRows; ++j) {
-        const int64_t r = threadIdx.x + (int64_t)j * kOne;
-        if (r < a.n) {
-          const double* Vr = a.V + r * kGmresLd + i0;
-#pragma unroll
-          for (int c = 0; c < kDotW; ++c)
-            if (i0 + c <= k) acc[c] = fma(Vr[c], wr[j], acc[c]);
+          for (int j = 0; j < kRows; ++j) {
+            const int64_t r = threadIdx.x + (int64_t)j * kOne;
+            if (r < a.n) acc[c] = fma(a.V[(i0 + c) * a.n + r], wr[j], acc[c]);
+          }
         }
       }
-      group_sum<kDotW>(acc, s_part, h + i0);
+      group_sum8(acc, s_part[buf], o, h + i0);
+      buf ^= 1;
     }
-    double hc[kVC];
-#pragma unroll
-    for (int c = 0; c < kVC; ++c) hc[c] = h[c];
+    double t[kRows];
 #pragma unroll
     for (int j = 0; j < kRows; ++j) {
-      const int64_t r = threadIdx.x + (int64_t)j * kOne;
-      double t = 0.0;
+      t[j] = 0.0;
 #pragma unroll
-      for (int c = 0; c < kVC; ++c) t = fma(vc[j][c], hc[c], t);
-      if (r < a.n) {
-        const double* Vr = a.V + r * kGmresLd;
-        for (int i = kVC; i <= k; ++i) t = fma(Vr[i], h[i], t);
+      for (int c = 0; c < kVC; ++c) t[j] = fma(vc[j][c], hc[c], t[j]);
+    }
+    if (k >= kVC) {
+      __syncthreads();   // h is written
+      for (int i = kVC; i <= k; ++i) {
+        const double hi = h[i];
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) {
+          const int64_t r = threadIdx.x + (int64_t)j * kOne;
+          if (r < a.n) t[j] = fma(a.V[i * a.n + r], hi, t[j]);
+        }
       }
-      wr[j] -= t;
     }
-  }
-  double nn[1] = {0.0};
 #pragma unroll
-  for (int j = 0; j < kRows; ++j) nn[0] = fma(wr[j], wr[j], nn[0]);
-  group_sum<1>(nn, s_part, s_n);
+    for (int j = 0; j < kRows; ++j) wr[j] -= t[j];
+  }
+  double nn = 0.0;
+#pragma unroll
+  for (int j = 0; j < kRows; ++j) nn = fma(wr[j], wr[j], nn);
+  const double nrm = sqrt(group_sum(nn, s_part[buf]));
   if (threadIdx.x == 0) {
-    const double nrm = sqrt(s_n[0]);
-    double* hk = s_hk;
-    for (int i = 0; i <= k; ++i) hk[i] = s_h[0][i] + s_h[1][i];
-    hk[k + 1] = nrm;
+    double* Hk = st->H + (int64_t)k * (kGmresLd + 1);
+    double cur = s_h[0][0] + s_h[1][0];   // H[i][k] after the rotations before i
     for (int i = 0; i < k; ++i) {
-      const double t0 = s_cs[i] * hk[i] + s_sn[i] * hk[i + 1];
-      hk[i + 1] = -s_sn[i] * hk[i] + s_cs[i] * hk[i + 1];
-      hk[i] = t0;
+      const double nx = s_h[0][i + 1] + s_h[1][i + 1], cs = s_cs[i], sn = s_sn[i];
+      Hk[i] = cs * cur + sn * nx;
+      cur = -sn * cur + cs * nx;
     }
-    const double den = hypot(hk[k], hk[k + 1]);
+    const double den = hypot(cur, nrm);
     double c = 1.0, sn = 0.0;
     if (den > 0.0) {
-      c = hk[k] / den;
-      sn = hk[k + 1] / den;
+      c = cur / den;
+      sn = nrm / den;
     }
-    hk[k] = den;
-    hk[k + 1] = 0.0;
-    double* Hk = st->H + (int64_t)k * (kGmresLd + 1);
-    for (int i = 0; i <= k + 1; ++i) Hk[i] = hk[i];
+    Hk[k] = den;
+    Hk[k + 1] = 0.0;
     st->cs[k] = c;
     st->sn[k] = sn;
     const double gk1 = -sn * s_sc[0];
@@ -627,16 +679,17 @@ __global__ __launch_bounds__(kOne) void k_bg_orth(GmresArgs a, const double* __r
     st->stop = stop;
     st->halt = stop | fail;
     st->skip_true = !stop | fail;
-    s_next = !(stop | fail) && nrm > 0.0 && k + 1 < kGmresLd;
-    s_scale = nrm > 0.0 ? 1.0 / nrm : 0.0;
   }
-  __syncthreads();
-  if (s_next) store_basis<kRows>(a, k + 1, wr, s_scale, zv);
+  // stored without waiting for the stop rules: after a stop or a failure nothing
+  // reads column k + 1 or zv before a new cycle writes them
+  if (nrm > 0.0 && k + 1 < kGmresLd) store_basis<kRows>(a, k + 1, wr, 1.0 / nrm, zv);
 }
 
-// End of a stopped cycle: y = R^-1 g (wave 0, back substitution), x += Z y.
-__global__ __launch_bounds__(kOne) void k_bg_update(GmresArgs a) {
-  GmresState* st = a.st;
+// End of a stopped cycle: y = R^-1 g (wave 0 of each workgroup, back substitution),
+// x += Z y, one row per thread.
+constexpr int kUpdThreads = 256;
+__global__ __launch_bounds__(kUpdThreads) void k_bg_update(GmresArgs a) {
+  const GmresState* st = a.st;
   if (!st->stop || st->done || st->fail) return;
   const int k = st->k;
   if (k <= 0) return;
@@ -645,7 +698,7 @@ __global__ __launch_bounds__(kOne) void k_bg_update(GmresArgs a) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   constexpr int ldh = kGmresLd + 1;
   // the leading k columns of the triangular factor, in LDS (parallel loads)
-  for (int e = threadIdx.x; e < k * ldh; e += kOne) s_H[e] = st->H[e];
+  for (int e = threadIdx.x; e < k * ldh; e += kUpdThreads) s_H[e] = st->H[e];
   if (w == 0) s_y[lane] = lane < k ? st->g[lane] : 0.0;
   __syncthreads();
   if (w == 0) {
@@ -658,12 +711,12 @@ __global__ __launch_bounds__(kOne) void k_bg_update(GmresArgs a) {
     s_y[lane] = lane < k ? yi : 0.0;
   }
   __syncthreads();
-  for (int64_t r = threadIdx.x; r < a.n; r += kOne) {
-    const double* Zr = a.Z + r * kGmresLd;
-    double d = 0.0;
-    for (int i = 0; i < k; ++i) d = fma(Zr[i], s_y[i], d);
-    a.x[r] += d;
-  }
+  const int64_t r = blockIdx.x * (int64_t)kUpdThreads + threadIdx.x;
+  if (r >= a.n) return;
+  double d = 0.0;
+#pragma unroll 8
+  for (int i = 0; i < k; ++i) d = fma(a.Z[i * a.n + r], s_y[i], d);
+  a.x[r] += d;
 }
 
 }  // namespace
@@ -725,13 +778,14 @@ hipError_t launch_prec_block(const GmresArgs& a, int32_t M, int64_t N, const int
                              const double* blocks, double* zv, bool begin, hipStream_t s) {
   if (begin)
     hipLaunchKernelGGL(k_prec_begin, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a, zv);
+  const int64_t zr = begin ? kGmresLd : 1, zc = begin ? 1 : a.n;
   if (M > 0) {
     if (Y)
       hipLaunchKernelGGL(k_prec_block<true>, dim3((unsigned)M), dim3(kPrecThreads), 0, s, a, N, off,
-                         nb_lim, nb_model, Y, blocks, kBlockStride, zv);
+                         nb_lim, nb_model, Y, blocks, kBlockStride, zr, zc, zv);
     else
       hipLaunchKernelGGL(k_prec_block<false>, dim3((unsigned)M), dim3(kPrecThreads), 0, s, a, N,
-                         off, nb_lim, nb_model, Y, blocks, kBlockStride, zv);
+                         off, nb_lim, nb_model, Y, blocks, kBlockStride, zr, zc, zv);
   }
   return hipGetLastError();
 }
@@ -758,7 +812,8 @@ hipError_t launch_bg_orth(const GmresArgs& a, const double* Aw, double* zv, hipS
 
 hipError_t launch_bg_update(const GmresArgs& a, hipStream_t s) {
   if (a.n > kGmresSmallN) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_bg_update, dim3(1), dim3(kOne), 0, s, a);
+  hipLaunchKernelGGL(k_bg_update, dim3((unsigned)((a.n + kUpdThreads - 1) / kUpdThreads)),
+                     dim3(kUpdThreads), 0, s, a);
   return hipGetLastError();
 }
 
