@@ -655,4 +655,53 @@ hipError_t launch_field(const FieldPlan& fp, int64_t P, int64_t Q, const double*
 hipError_t launch_tracer_combine(int64_t P, double* y, const double* K1, const double* K2,
                                  const double* K3, const double* K4, double dt, hipStream_t s);
 
+// ---- sums over a wave in FP64 without LDS ----
+template <int CTRL>
+__device__ inline double dpp64(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+// {a, b} -> {a.lanes 0-31, b.lanes 0-31} + {a.lanes 32-63, b.lanes 32-63} (W = 32),
+// the same by rows of 16 lanes (W = 16).
+template <int W>
+__device__ inline double fold(double a, double b) {
+  typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+  uint2v lo, hi;
+  if constexpr (W == 32) {
+    lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  } else {
+    lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  }
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// Sum over each row of 16 lanes, in every lane of it.
+__device__ inline double row_sum(double v) {
+  v += dpp64<0xB1>(v);    // quad_perm 1 0 3 2
+  v += dpp64<0x4E>(v);    // quad_perm 2 3 0 1
+  v += dpp64<0x141>(v);   // row_half_mirror
+  return v + dpp64<0x128>(v);   // row_ror 8
+}
+
+// Sums over the wave of eight values at once: lane l has that of v[wave_sum8_of(l)].
+// Each step halves the values a lane carries instead of summing each over all
+// lanes: 34 instructions instead of 48 shuffles.
+__device__ inline int wave_sum8_of(int lane) {
+  return 4 * (lane >> 5) + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1);
+}
+__device__ inline double wave_sum8(const double (&v)[8]) {
+  double a[4], b[2];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) a[c] = fold<32>(v[c], v[c + 4]);
+#pragma unroll
+  for (int c = 0; c < 2; ++c) b[c] = fold<16>(a[c], a[c + 2]);
+  const bool up = threadIdx.x & 8;
+  double t = (up ? b[1] : b[0]) + dpp64<0x128>(up ? b[0] : b[1]);   // row_ror 8
+  t += dpp64<0x141>(t);
+  t += dpp64<0xB1>(t);
+  return t + dpp64<0x4E>(t);
+}
+
 }  // namespace nrs

@@ -392,35 +392,6 @@ constexpr int kOne = 1024;
 // hold only the registers they use
 inline int rows_for(int64_t n) { return n <= 4 * kOne ? 4 : 8; }
 
-template <int CTRL>
-__device__ inline double dpp64(double v) {
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
-}
-// {a, b} -> {a.lanes 0-31, b.lanes 0-31} + {a.lanes 32-63, b.lanes 32-63} (W = 32),
-// the same by rows of 16 lanes (W = 16).
-template <int W>
-__device__ inline double fold(double a, double b) {
-  typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-  uint2v lo, hi;
-  if constexpr (W == 32) {
-    lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
-    hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
-  } else {
-    lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
-    hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
-  }
-  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
-// Sum over each row of 16 lanes, in every lane of it.
-__device__ inline double row_sum(double v) {
-  v += dpp64<0xB1>(v);    // quad_perm 1 0 3 2
-  v += dpp64<0x4E>(v);    // quad_perm 2 3 0 1
-  v += dpp64<0x141>(v);   // row_half_mirror
-  return v + dpp64<0x128>(v);   // row_ror 8
-}
-
 // out = sum over the workgroup of v, in every thread; one barrier.  part [16] must not be
 // the buffer of the sum before (a slow wave may still read it).
 __device__ inline double group_sum(double v, double* __restrict__ part) {
@@ -434,24 +405,12 @@ __device__ inline double group_sum(double v, double* __restrict__ part) {
 }
 
 // out[c] = sum over the workgroup of v[c] (c < 8), in every thread; also into h[0..8) for
-// reads after the next barrier (wave 0's lanes).  Each step of a wave's sum halves the
-// values a lane carries instead of summing each over all lanes: 34 instructions
-// instead of 48 shuffles.  One barrier; part [128] as above.
+// reads after the next barrier (wave 0's lanes).  One barrier; part [128] as above.
 __device__ inline void group_sum8(const double (&v)[8], double* __restrict__ part,
                                   double (&out)[8], double* __restrict__ h) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  double a[4], b[2];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) a[c] = fold<32>(v[c], v[c + 4]);
-#pragma unroll
-  for (int c = 0; c < 2; ++c) b[c] = fold<16>(a[c], a[c + 2]);
-  const bool up = lane & 8;
-  double t = (up ? b[1] : b[0]) + dpp64<0x128>(up ? b[0] : b[1]);   // row_ror 8
-  t += dpp64<0x141>(t);
-  t += dpp64<0xB1>(t);
-  t += dpp64<0x4E>(t);
-  if ((lane & 7) == 0)   // this lane group's column
-    part[w * 8 + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1)] = t;
+  double t = wave_sum8(v);
+  if ((lane & 7) == 0) part[w * 8 + wave_sum8_of(lane)] = t;
   __syncthreads();
   t = part[lane] + part[lane + 64];   // column lane & 7, sixteen waves
   t += dpp64<0x128>(t);
