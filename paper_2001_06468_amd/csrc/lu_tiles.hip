@@ -256,7 +256,6 @@ __device__ __attribute__((noinline)) void diag_factor(Shared<T>& S, const LuSys<
         }
 #pragma unroll
         for (int c = k + 2; c < kPW; ++c) v[c] -= l * lane_value<T>(v[c], p);
-        if (lane == 0) S.perm[c0 + k] = p;
       }
 #pragma unroll
       for (int k = 0; k < kPW; ++k) S.Cs[(c0 + k) * kCS + lane] = v[k];
@@ -265,6 +264,7 @@ __device__ __attribute__((noinline)) void diag_factor(Shared<T>& S, const LuSys<
       if (lane == 0) S.live[b & 1] = ~um;
       if (used && myj >= c0) {
         const int kp = myj - c0;
+        S.perm[myj] = lane;
 #pragma unroll
         for (int k = 0; k < kPW; ++k) Lp[k * kPW + kp] = k < kp ? v[k] : T(0);
       }
