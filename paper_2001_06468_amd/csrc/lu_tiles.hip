@@ -100,11 +100,13 @@ __device__ inline T ld_pad(const T* A, int64_t lda, int64_t n, int64_t r, int64_
 }
 
 // 32-bit pivot key: |v| rounded to FP32, its low 6 mantissa bits replaced by
-// (63 - lane), so the maximum is unique and ties go to the lowest lane.
+// (63 - lane), so the maximum is unique and ties go to the lowest lane; the
+// sign bit is set, so that 0 (a row already used) is below every key.  code =
+// pivot_code(lane); the lane of a key is ~key & 63.
+__device__ inline uint32_t pivot_code(int lane) { return 0x80000000u | (uint32_t)(63 - lane); }
 template <class T>
-__device__ inline uint32_t pivot_key(T v, int lane) {
-  const float a = fabsf((float)v);
-  return (__float_as_uint(a) & ~63u) | (uint32_t)(63 - lane);
+__device__ inline uint32_t pivot_key(T v, uint32_t code) {
+  return (__float_as_uint((float)v) & 0x7fffffc0u) | code;
 }
 
 // Maximum of a 32-bit value over the 64 lanes of the wave (DPP row
@@ -217,6 +219,10 @@ __device__ inline void unit_lower_subst16(C (&x)[16], const T* L, int rs) {
 // the remaining tiles meanwhile (one barrier per panel).  Afterwards the rows
 // stay in physical order; the caller stores physical row r at logical row
 // S.pos[r].
+// What bounds it: the issue of one wave's chain of pivot steps (about 50 instructions
+// each), a third of a band's 27 us.  With each step's pivot row stored from lane 0, its
+// reciprocal taken after the search and lane reads beside the products, n = 3150
+// took 1478 us (1381 us so) and n = 6123 3187 us (3057 us so).
 constexpr int kPW = 16;
 
 template <class T>
@@ -235,12 +241,18 @@ __device__ __attribute__((noinline)) void diag_factor(Shared<T>& S, const LuSys<
       T v[kPW];
 #pragma unroll
       for (int k = 0; k < kPW; ++k) v[k] = S.Cs[(c0 + k) * kCS + lane];
-      uint32_t key = used ? 0u : pivot_key(v[0], lane) + 1u;
+      const uint32_t code = pivot_code(lane);
+      uint32_t key = used ? 0u : pivot_key(v[0], code);
 #pragma unroll
       for (int k = 0; k < kPW; ++k) {
+        // every row's reciprocal, beside the search: the pivot's is then one lane read
+        const T rec = pivot_inverse<T>(v[k]);
         const uint32_t best = wave_max_u32(key);
-        const int p = __builtin_amdgcn_readfirstlane(63 - (int)((best - 1u) & 63u));
-        const T piv = lane_value<T>(v[k], p);
+        const int p = (int)(~best & 63u);
+        const T inv = lane_value<T>(rec, p), piv = lane_value<T>(v[k], p);
+        T pr[kPW];
+#pragma unroll
+        for (int c = k + 1; c < kPW; ++c) pr[c] = lane_value<T>(v[c], p);
         if (lane == p) {
           used = true;
           myj = c0 + k;
@@ -248,14 +260,17 @@ __device__ __attribute__((noinline)) void diag_factor(Shared<T>& S, const LuSys<
         // rows already used (and the pivot row) get l = 0 and stay unchanged
         const bool upd = !used && piv != T(0);
         zero = zero || piv == T(0);
-        const T l = upd ? v[k] * pivot_inverse<T>(piv) : T(0);
+        const T l = upd ? v[k] * inv : T(0);
         v[k] = upd ? l : v[k];
+        // the lane reads stay together in front of the products, which then fill the waits
+        // between the steps of the next search (else each product waits for its read)
+        __builtin_amdgcn_sched_barrier(0);
         if (k + 1 < kPW) {
-          v[k + 1] -= l * lane_value<T>(v[k + 1], p);
-          key = used ? 0u : pivot_key(v[k + 1], lane) + 1u;
+          v[k + 1] -= l * pr[k + 1];
+          key = used ? 0u : pivot_key(v[k + 1], code);
         }
 #pragma unroll
-        for (int c = k + 2; c < kPW; ++c) v[c] -= l * lane_value<T>(v[c], p);
+        for (int c = k + 2; c < kPW; ++c) v[c] -= l * pr[c];
       }
 #pragma unroll
       for (int k = 0; k < kPW; ++k) S.Cs[(c0 + k) * kCS + lane] = v[k];
