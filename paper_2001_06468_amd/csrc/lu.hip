@@ -629,6 +629,22 @@ __device__ inline void st_release(int32_t* p, int32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A system's descriptor, its pointers known to be to global memory (with flat loads the
+// FP64 passes took 344 + 282 us at n = 3150, 319 + 239 us so).
+template <class T>
+__device__ inline TrsvSys<T> global_sys(const TrsvSys<T>& y) {
+  TrsvSys<T> r = y;
+  r.LU = as_global(y.LU);
+  r.x = as_global(y.x);
+  r.rhs = as_global(y.rhs);
+  r.perm = as_global(y.perm);
+  r.flags = as_global(y.flags);
+  r.stop = as_global(y.stop);
+  r.epoch = as_global(y.epoch);
+  r.xp = as_global(y.xp);
+  return r;
+}
+
 // LOCALP: the factors come from the tile LU with static block pivoting; the
 // interchanges of block row b (lperm, block-local) are applied to the
 // partial result b_b - sum_k L_bk y_k before the diagonal solve.
@@ -648,7 +664,7 @@ __global__ __launch_bounds__(kTrsvThreads) void k_trsv(TrsvBatch<T> bt, int32_t*
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   if (tid == 0) s_t = atomicAdd(&ctl[0], 1);
   __syncthreads();
-  const int32_t tk = s_t;
+  const int32_t tk = __builtin_amdgcn_readfirstlane(s_t);
   int64_t kstep;
   int sidx;
   if (bt.sys == nullptr) {
@@ -663,7 +679,7 @@ __global__ __launch_bounds__(kTrsvThreads) void k_trsv(TrsvBatch<T> bt, int32_t*
     kstep = lo / bt.B;
     sidx = lo % bt.B;
   }
-  const TrsvSys<T> sy = bt.sys ? bt.sys[sidx] : bt.one;
+  const TrsvSys<T> sy = bt.sys ? global_sys(bt.sys[sidx]) : global_sys(bt.one);
   const bool skip = tk >= bt.total || (sy.stop && *sy.stop);
   const int64_t n = sy.n, lda = sy.lda;
   const T* __restrict__ LU = sy.LU;
@@ -893,10 +909,11 @@ __global__ __launch_bounds__(kTrsvThreads) void k_trsv32(TrsvBatch<float> bt,
   __shared__ int s_pc[kTb];        // column of s_di that holds column c of D^-1
   __shared__ float s_l[kTb][kLd];  // A_bl (row-major), then M
   __shared__ float s_w[kTrsvThreads / 64][16];  // per-wave copy of the polled values
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (tid == 0) s_t = atomicAdd(&ctl[0], 1);
   __syncthreads();
-  const int32_t tk0 = s_t;
+  const int32_t tk0 = __builtin_amdgcn_readfirstlane(s_t);
   const bool UPPER = tk0 >= bt.total;
   const int32_t tk = UPPER ? tk0 - bt.total : tk0;
   int64_t kstep;
@@ -913,7 +930,8 @@ __global__ __launch_bounds__(kTrsvThreads) void k_trsv32(TrsvBatch<float> bt,
     kstep = lo / bt.B;
     sidx = lo % bt.B;
   }
-  const TrsvSys<float> sy = bt.sys ? bt.sys[min(sidx, bt.B - 1)] : bt.one;
+  const TrsvSys<float> sy =
+      bt.sys ? global_sys(bt.sys[min(sidx, bt.B - 1)]) : global_sys(bt.one);
   const bool skip = tk >= bt.total || (sy.stop && *sy.stop);
   if (!skip) {
     const int64_t n = sy.n, lda = sy.lda;

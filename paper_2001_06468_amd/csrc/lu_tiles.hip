@@ -226,10 +226,11 @@ __device__ inline void unit_lower_subst16(C (&x)[16], const T* L, int rs) {
 constexpr int kPW = 16;
 
 template <class T>
-__device__ __attribute__((noinline)) void diag_factor(Shared<T>& S, const LuSys<T>& sy, int64_t m,
-                                                      int32_t* sing) {
+__device__ __attribute__((noinline)) void diag_factor(Shared<T>& S, int32_t* lperm,
+                                                      int64_t n, int64_t m, int32_t* sing) {
   typedef typename Mf<T>::acc_t acc_t;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   bool used = false, zero = false;  // wave 0 only
   int myj = 0;
 #pragma unroll
@@ -336,7 +337,7 @@ __device__ __attribute__((noinline)) void diag_factor(Shared<T>& S, const LuSys<
   if (tid < TB) {
     const int64_t r0 = m * TB;
     const int64_t gj = r0 + tid;
-    if (gj < sy.n) sy.lperm[gj] = (int32_t)(r0 + S.perm[tid]);
+    if (gj < n) lperm[gj] = (int32_t)(r0 + S.perm[tid]);
   }
 }
 
@@ -354,7 +355,8 @@ __device__ __attribute__((noinline)) void diag_factor(Shared<T>& S, const LuSys<
 template <class T>
 __device__ __attribute__((noinline)) void col_solve(Shared<T>& S) {
   typedef typename Mf<T>::acc_t acc_t;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, li = lane & 15;
+  const int lane = threadIdx.x & 63, g = lane >> 4, li = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   T* col = S.Cs + (w * 16 + li) * kCS;
   T* DI = S.Ws + TB * kLS;  // inverses of the diagonal blocks: block b, (i, k) at b*272 + i*17 + k
   {  // rows to logical order in this wave's columns (all loads before stores)
@@ -437,7 +439,8 @@ __device__ __attribute__((noinline)) void row_solve(Shared<T>& S) {
   typedef typename Mf<T>::acc_t acc_t;
   // XT: the tile is the hand-over tile in dynamic LDS instead of S.Cs
   T* const Ct = XT ? reinterpret_cast<T*>(lu_xtile) : S.Cs;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, li = lane & 15;
+  const int lane = threadIdx.x & 63, g = lane >> 4, li = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r0 = w * 16;
   T* UI = S.Ws + TB * kLS;  // inverses of Uh's diagonal blocks: block b, (k, j) at b*272 + k*17 + j
   if (lane < 16) {  // wave w: row `lane` of the inverse of diagonal block w (in FP64)
@@ -516,7 +519,7 @@ __device__ __attribute__((noinline)) void row_solve(Shared<T>& S) {
 // them in scratch memory; with the launch, n = 126 went 84.8 -> 72.3 us, n = 3150
 // 1498 -> 1478 us.)
 template <class T>
-__device__ void diag_ipiv(Shared<T>& S, const LuSys<T>& sy, int64_t m) {
+__device__ __forceinline__ void diag_ipiv(Shared<T>& S, const LuSys<T>& sy, int64_t m) {
   if (threadIdx.x >= 64 || !sy.ipiv) return;
   const int lane = threadIdx.x & 63;
   const int mine = S.perm[lane];
@@ -616,7 +619,8 @@ template <class T, bool B16, bool XO>
 __device__ inline void run_task(Shared<T>& S, const LuSys<T>& sy, int64_t i,
                                                    int64_t j, int64_t m, int32_t* err) {
   typedef typename Mf<T>::acc_t acc_t;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // tasks on the diagonal chain issue ahead of other waves on their SIMDs
     const bool chain = i == j || i == j + 1 || j == i + 1;
     if (chain) __builtin_amdgcn_s_setprio(2);
@@ -723,7 +727,7 @@ __device__ inline void run_task(Shared<T>& S, const LuSys<T>& sy, int64_t i,
             if (lane == 0) S.task[2] = (int32_t)e;
           }
           __syncthreads();
-          kend = S.task[2];
+          kend = __builtin_amdgcn_readfirstlane(S.task[2]);
           issue(k, stage);
         }
         __builtin_amdgcn_s_waitcnt(kWaitVmem);  // this wave's share of term k has landed
@@ -837,7 +841,7 @@ __device__ inline void run_task(Shared<T>& S, const LuSys<T>& sy, int64_t i,
           if (lane == 0) S.task[2] = (int32_t)e;
         }
         __syncthreads();
-        kend = S.task[2];
+        kend = __builtin_amdgcn_readfirstlane(S.task[2]);
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
           const int c = c0 + 4 * q;
@@ -908,7 +912,7 @@ __device__ inline void run_task(Shared<T>& S, const LuSys<T>& sy, int64_t i,
     }
     __syncthreads();
     if (i == j) {
-      diag_factor<T>(S, sy, m, sy.sing);
+      diag_factor<T>(S, sy.lperm, n, m, sy.sing);
     } else if (i < j) {
       // U_mj = L_mm^-1 P_m C; L_mm staged column-major
       {
@@ -977,6 +981,20 @@ __device__ inline void run_task(Shared<T>& S, const LuSys<T>& sy, int64_t i,
     if (chain) __builtin_amdgcn_s_setprio(0);
 }
 
+template <class T>
+__device__ inline LuSys<T> global_sys(const LuSys<T>& y) {
+  LuSys<T> r = y;
+  r.A = as_global(y.A);
+  r.lperm = as_global(y.lperm);
+  r.ipiv = as_global(y.ipiv);
+  r.done = as_global(y.done);
+  r.sing = as_global(y.sing);
+  r.sh = as_global(y.sh);
+  r.pre = as_global(y.pre);
+  r.preflag = as_global(y.preflag);
+  return r;
+}
+
 // One workgroup per task.  The ticket, not blockIdx, decides the task, so a
 // workgroup only waits for tasks taken by workgroups that already run.
 // MINB = workgroups per CU the register budget must allow: 1 for a single
@@ -990,7 +1008,7 @@ __global__ __launch_bounds__(kLuThreads, MINB) void k_lu_tiles(LuBatch<T> bt, in
   int32_t* err = ctl + 2;
   if (tid == 0) S.task[0] = atomicAdd(&ctl[0], 1);
   __syncthreads();
-  const int32_t t = S.task[0];
+  const int32_t t = __builtin_amdgcn_readfirstlane(S.task[0]);
   if (t < bt.total) {
     // (band, part, system) of the ticket: last prefix entry <= t; the
     // off-diagonal part starts at p = 1.  One system: band m starts at
@@ -1027,7 +1045,11 @@ __global__ __launch_bounds__(kLuThreads, MINB) void k_lu_tiles(LuBatch<T> bt, in
       i = m + p / 2;
       j = m;
     }
-    const LuSys<T> sy = bt.sys ? bt.sys[s] : bt.one;
+    // t, and with it the system and the tile, is the same in every lane and held in scalar
+    // registers, and the pointers are known to be to global memory (per-lane tile
+    // indexes, and flat loads and stores, which wait for LDS accesses too: n = 3150
+    // 1381 -> 1316 us, n = 6123 3057 -> 2885 us)
+    const LuSys<T> sy = bt.sys ? global_sys(bt.sys[s]) : global_sys(bt.one);
     run_task<T, B16, MINB == 1>(S, sy, i, j, m, err);
     if (i == j) diag_ipiv<T>(S, sy, m);
   }
