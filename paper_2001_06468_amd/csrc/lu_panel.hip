@@ -23,12 +23,13 @@
 // magnitude, lowest row on ties; every entry takes its updates in increasing
 // pivot order; multipliers are correctly rounded quotients).
 //
-// Measured, FP64, per launch of W columns: 22.1 us (W = 16) at 512 rows, 23.5 us
-// at 1024, 26.8 us at 1536, 13.9 us (W = 8) at 2048, 16.8 us at 3072, 21.8 us at
-// 4096, i.e. 1.4 to 2.7 us a column; one grid-wide barrier per column took 4.4 us
-// (600 rows) to 5.5 us (3000 rows).  Per column about 2400 cycles, nearly all of it
-// issue and latency of some 300 dependent instructions on one or two waves per
-// SIMD.  Measured equal or slower: a rolled loop with the next column searched
+// Measured, FP64, per launch of W columns: 19.9 us (W = 16) at 512 rows, 21.9 us
+// at 1024, 24.1 us at 1536, 12.7 us (W = 8) at 2048, 15.5 us at 3072, 19.0 us at
+// 4096, i.e. 1.2 to 2.4 us a column; one grid-wide barrier per column took 4.4 us
+// (600 rows) to 5.5 us (3000 rows).  Nearly all of it is issue and latency of
+// dependent instructions on one or two waves per SIMD (with the update on one side of a
+// branch, which copied every register twice, and addresses formed per column: 22.1, 23.5,
+// 26.8, 13.9, 16.8 and 21.8 us).  Measured equal or slower: a rolled loop with the next column searched
 // ahead (one barrier and one LDS read a column, but twice the fused updates), four
 // waves of twice the rows, the interchange done in registers (copies at every
 // branch), 32 columns at 512 rows.
@@ -102,14 +103,15 @@ __device__ inline double lane_value(double v, int lane) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// |piv| far enough from the ends of the range that 1/piv and the remainder of
-// the corrected quotient below are normal numbers
+// |piv| (hi: its high word) far enough from the ends of the range that 1/piv and the
+// remainder of the corrected quotient below are normal numbers: about 1e-279 to
+// 1e279 in FP64, 1e-29 to 1e29 in FP32
 template <class T>
-__device__ inline bool plain_pivot(T a);
+__device__ inline bool plain_pivot(uint32_t hi);
 template <>
-__device__ inline bool plain_pivot<double>(double a) { return a > 1e-280 && a < 1e280; }
+__device__ inline bool plain_pivot<double>(uint32_t hi) { return hi - 0x06000000u < 0x73e00000u; }
 template <>
-__device__ inline bool plain_pivot<float>(float a) { return a > 1e-30f && a < 1e30f; }
+__device__ inline bool plain_pivot<float>(uint32_t hi) { return hi - 0x0f000000u < 0x61000000u; }
 
 // Element access through a buffer resource: offsets at or past the resource's
 // size read zero and store nothing, so rows past the panel need no branch.
@@ -298,10 +300,12 @@ __device__ inline void put_row(T* dst, const T (&a)[R][W], int r,
 // multiplier is 1), so finished rows are zero and need no mask.
 template <class T, int R, int W, int j>
 __device__ inline void eliminate_column(PanelLds<T, W>& S, T (&a)[R][W], int& pos, int wv,
-                                        int64_t m, int64_t kb, T* __restrict__ A, int64_t lda,
-                                        int32_t* __restrict__ ipiv, int32_t* __restrict__ sing) {
+                                        int64_t m, int64_t kb, T*& colp, T* __restrict__ rowp,
+                                        int64_t lda, int32_t* __restrict__ ipiv,
+                                        int32_t* __restrict__ sing) {
   if (j >= wv) return;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   // this thread's largest entry, the lowest row on ties (NaN is never chosen)
   T best = T(0);
   int br = 0;
@@ -335,47 +339,55 @@ __device__ inline void eliminate_column(PanelLds<T, W>& S, T (&a)[R][W], int& po
   } else if (((g >> 6) & (kPT / 64 - 1)) == wid && lane == (g & 63)) {
     put_row(S.row[j & 1], a, g / kPT, std::make_integer_sequence<int, R>{});
   }
-  const bool is_piv = none ? pos == j : g == tid;
+  const bool is_piv = (none ? pos : tid) == (none ? j : g);
   __syncthreads();
   const T ul = S.row[j & 1][lane & (W - 1)];
+  const T uz = none ? T(0) : ul;   // nothing is eliminated without a pivot
   T u[W];
 #pragma unroll
-  for (int c = j; c < W; ++c) u[c] = lane_value(ul, c);
+  for (int c = j; c < W; ++c) u[c] = lane_value(uz, c);
   const T piv = u[j];
   if (wid == 0) {
     // the pivot row is final: its multipliers and its U part
-    if (lane < wv) A[kb + j + (kb + lane) * lda] = ul;
-    if (lane == 0) {
+    if (lane < wv) rowp[j] = ul;
+    if (lane == j) {
       ipiv[kb + j] = (int32_t)(kb + p);
-      if (piv == T(0)) atomicOr(sing, 1);
+      if (ul == T(0)) atomicOr(sing, 1);
     }
   }
-  if (!none) {
+  // One path for all columns: with the update on one side of a branch only, the whole
+  // of a[][] was copied to other registers and back for each column.
+  if (plain_pivot<T>((uint32_t)khi)) {
+    // quotient by the reciprocal, corrected by its remainder: the correctly
+    // rounded quotient
     const T inv = T(1) / piv;
-    if (plain_pivot<T>(fabs(piv))) {
-      // quotient by the reciprocal, corrected by its remainder: the correctly
-      // rounded quotient
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const T q = a[r][j] * inv;
-        a[r][j] = fma(fma(-q, piv, a[r][j]), inv, q);
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < R; ++r) a[r][j] = a[r][j] / piv;
+    for (int r = 0; r < R; ++r) {
+      const T q = a[r][j] * inv;
+      a[r][j] = fma(fma(-q, piv, a[r][j]), inv, q);
     }
+  } else if (!none) {
 #pragma unroll
-    for (int c = j + 1; c < W; ++c)
+    for (int r = 0; r < R; ++r) a[r][j] = a[r][j] / piv;
+  }
 #pragma unroll
-      for (int r = 0; r < R; ++r) a[r][c] -= a[r][j] * u[c];
-  } else if (is_piv) {
+  for (int r = 0; r < R; ++r) {
+    const T l = none ? T(0) : a[r][j];
 #pragma unroll
-    for (int c = j + 1; c < W; ++c) a[0][c] = T(0);
+    for (int c = j + 1; c < W; ++c) a[r][c] -= l * u[c];
+  }
+  if (none) {
+    asm volatile("; no pivot");   // a branch, not two selects per column
+    if (is_piv) {
+#pragma unroll
+      for (int c = j + 1; c < W; ++c) a[0][c] = T(0);
+    }
   }
   pos = is_piv ? -1 : (pos == j ? p : pos);
   // the first W rows are stored when they become pivots or at the end; what a
   // pivot row stores here is overwritten by the row that takes its place
-  const Column<T> col(A + kb + (kb + j) * lda, m);
+  const Column<T> col(colp, m);
+  colp += lda;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     if (r == 0) {
@@ -391,7 +403,9 @@ __device__ inline void eliminate(PanelLds<T, W>& S, T (&a)[R][W], int& pos, int 
                                  int64_t kb, T* __restrict__ A, int64_t lda,
                                  int32_t* __restrict__ ipiv, int32_t* __restrict__ sing,
                                  std::integer_sequence<int, J...>) {
-  (eliminate_column<T, R, W, J>(S, a, pos, wv, m, kb, A, lda, ipiv, sing), ...);
+  T* colp = A + kb + kb * lda;                           // column j, from row kb
+  T* rowp = A + kb + (kb + (threadIdx.x & 63)) * lda;    // this lane's column of row kb + j
+  (eliminate_column<T, R, W, J>(S, a, pos, wv, m, kb, colp, rowp, lda, ipiv, sing), ...);
 }
 
 // Factors columns kb .. kb+wv-1 (rows kb .. n-1) after applying the sub-panel
