@@ -168,14 +168,20 @@ struct PanelLds {
 };
 
 // x <- L^-1 x for the unit lower W x W block in S.L, one column per row of 16
-// lanes (lane q: entry q)
+// lanes (lane q: entry q).  Entry Q leaves the entries up to it as they are, by a
+// select: a zero multiplier would make them NaN where it is infinite.
 template <class T, int W, int... Q>
 __device__ inline T lower_solve16(const PanelLds<T, W>& S, T x, int q,
                                   std::integer_sequence<int, Q...>) {
   T l[W];
 #pragma unroll
   for (int t = 0; t < W; ++t) l[t] = (q > t && q < W) ? S.L[t * W + q] : T(0);
-  ((x -= l[Q] * row16_bcast<Q>(x)), ...);
+  const auto step = [&](auto at) {
+    constexpr int t = decltype(at)::value;
+    const T v = x - l[t] * row16_bcast<t>(x);
+    x = q > t ? v : x;
+  };
+  (step(std::integral_constant<int, Q>{}), ...);
   return x;
 }
 

@@ -117,3 +117,15 @@ def test_rows_above_an_infinity_stay_finite(ctx):
     LU, ipiv, _, _ = _factor(ctx, A0, torch.float64)
     np.testing.assert_array_equal(ipiv[:64], np.arange(64))
     assert bool(torch.isfinite(LU[:30, :]).all()) and bool(torch.isinf(LU[30, 100]))
+
+
+@pytest.mark.parametrize("n,row,col", [(130, 30, 40), (130, 0, 63), (1700, 10, 20), (4200, 5, 9)])
+def test_rows_above_an_infinity_stay_finite_inside_a_panel(ctx, n, row, col):
+    """The same for a column of the same 64-column panel, in a later sub-panel (16, 8
+    and 4 columns wide at these sizes): only the rows at and below it change."""
+    A0 = np.random.default_rng(10).normal(size=(n, n)) + 4 * n * np.eye(n)
+    A0[row, col] = np.inf
+    LU, ipiv, _, _ = _factor(ctx, A0, torch.float64)
+    # the column is eliminated as it is until its own pivot, so earlier pivots stay
+    np.testing.assert_array_equal(ipiv[:col], np.arange(col))
+    assert bool(torch.isfinite(LU[:row, col]).all()) and bool(torch.isinf(LU[row, col]))
