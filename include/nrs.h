@@ -353,7 +353,8 @@ nrs_status nrs_solve_batched(nrs_ctx* ctx, int32_t B, const nrs_problem* problem
  *        LAPACK order; for scope 1 the interchanges stay inside a tile);
  *   perm [n] int32: scope 0: the composite permutation, (P b)[i] = b[perm[i]];
  *        scope 1: logical row i of its tile came from original row perm[i];
- *   singular_flag [1] int32: bit 0 set if an exact zero pivot is met, bit 1
+ *   singular_flag [1] int32: bit 0 set if an exact zero pivot is met (scope 0:
+ *        also where a column is left with zeros and NaN only), bit 1
  *        if a bounded wait between the workgroups of a partial-pivoting
  *        panel timed out (left untouched otherwise; the caller clears it).
  * ws: device workspace of at least nrs_lu_factor_workspace_size(n, precision)

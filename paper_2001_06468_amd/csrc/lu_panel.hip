@@ -335,7 +335,9 @@ __device__ inline void eliminate_column(PanelLds<T, W>& S, T (&a)[R][W], int& po
   const int klo = __builtin_amdgcn_readlane(cd.y, pw);
   int p = __builtin_amdgcn_readlane(cd.z, pw);
   const int g = __builtin_amdgcn_readlane(cd.w, pw);
-  const bool none = (khi | klo) == 0;   // no non-zero finite entry: row j stays
+  // no entry but zeros and NaN: row j stays, and the matrix counts as singular (whether
+  // the zero or the NaN lies in row j)
+  const bool none = (khi | klo) == 0;
   if (none) {
     p = j;
     if (pos == j) {
@@ -358,7 +360,7 @@ __device__ inline void eliminate_column(PanelLds<T, W>& S, T (&a)[R][W], int& po
     if (lane < wv) rowp[j] = ul;
     if (lane == j) {
       ipiv[kb + j] = (int32_t)(kb + p);
-      if (ul == T(0)) atomicOr(sing, 1);
+      if (none) atomicOr(sing, 1);
     }
   }
   // One path for all columns: with the update on one side of a branch only, the whole

@@ -129,3 +129,17 @@ def test_rows_above_an_infinity_stay_finite_inside_a_panel(ctx, n, row, col):
     # the column is eliminated as it is until its own pivot, so earlier pivots stay
     np.testing.assert_array_equal(ipiv[:col], np.arange(col))
     assert bool(torch.isfinite(LU[:row, col]).all()) and bool(torch.isinf(LU[row, col]))
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("row", [20, 21, 60])
+def test_panel_zero_column_with_a_nan_is_singular(ctx, dtype, row):
+    """A column of zeros and one NaN has no pivot: the flag is raised wherever the NaN
+    lies, the diagonal row included."""
+    n = 70
+    A0 = np.random.default_rng(11).normal(size=(n, n)) + 4 * n * np.eye(n)
+    A0[:, 20] = 0.0
+    A0[row, 20] = np.nan
+    _, ipiv, _, sing = _factor(ctx, A0, dtype)
+    assert sing == 1
+    np.testing.assert_array_equal(ipiv[:20], np.arange(20))
