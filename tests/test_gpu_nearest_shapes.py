@@ -53,3 +53,29 @@ def test_nearest_shapes(Q, kind):
     nu = torch.empty(Q, dtype=torch.int32, device=DEV)
     nrs.nrs_nearest(ctx, T(x), off, T(X), T(g, torch.int32), nu)
     np.testing.assert_array_equal(nu.cpu().numpy(), _reference(x, X, off, g))
+
+
+def test_nearest_cost_does_not_depend_on_the_order_of_groups():
+    """Neighbouring points of distant groups take no more distances than sorted ones (400
+    groups of 40: 40 a point; all that lie between the groups of four points are 150
+    times as many).  The bound of 6 leaves room for launches and scattered loads."""
+    rng = np.random.default_rng(0)
+    G, k, Q = 400, 40, 40000
+    x, X = T(rng.normal(size=(3, G * k))), T(rng.normal(size=(3, Q)))
+    off = (np.arange(G + 1) * k).astype(np.int32)
+    ctx = nrs.Context(0)
+    nu = torch.empty(Q, dtype=torch.int32, device=DEV)
+    ms = []
+    for g in (np.sort(np.arange(Q) % G), rng.integers(0, G, size=Q)):
+        gx = T(g, torch.int32)
+        e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        times = []
+        for _ in range(4):   # the first as a warm-up
+            e0.record()
+            for _ in range(20):
+                nrs.nrs_nearest(ctx, x, off, X, gx, nu)
+            e1.record()
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1))
+        ms.append(min(times[1:]))
+    assert ms[1] <= 6 * ms[0], ms
