@@ -272,12 +272,15 @@ __global__ void k_rhs_batch(const BatchSys* __restrict__ sys, const int64_t* __r
 // points and chunk 8k + x, so an XCD's L2 holds its eighth of the sources.  Wave w
 // sums a contiguous quarter of its chunk, the four wave sums are added in a fixed
 // order.
-// What bounds it: FP64 issue (26 instructions and a quarter-rate reciprocal square
-// root per pair), and below about 10^7 pairs the launch and the scalar loads' latency,
-// hence the short chunks of apply_plan().  Against gathering 64-byte source records
-// first and the tracers' chunks of 256 sources (mean over calls, converged ones
-// that exit included): one filament (40 x 400 pairs) 16.5 -> 5.9 us, 25 filaments
-// (1000 x 10,000) 21.6 -> 14.3 us, 100 filaments (4000 x 40,000) 100.8 -> 102.9 us.
+// What bounds it: FP64 issue (24 instructions and a quarter-rate reciprocal square
+// root per pair, 3 per segment), and below about 10^7 pairs the launch and the scalar
+// loads' latency, hence the short chunks of apply_plan().  The factor of a segment's force
+// density is summed over the segment and applied once: applied pair by pair, 26
+// instructions, 13,000 x 130,000 pairs took 1687 us a call (1600 us so; 1615 us with gathered
+// records); only segments of one or two points lose by it (4000 of one: 34.8 -> 36.6 us).  Against gathering
+// 64-byte source records first and the tracers' chunks of 256 sources (mean over calls, converged
+// ones that exit included): one filament (40 x 400 pairs) 16.5 -> 5.7 us, 25 filaments
+// (1000 x 10,000) 21.6 -> 13.8 us, 100 filaments (4000 x 40,000) 100.8 -> 99.8 us.
 constexpr int kPairThreads = 256;
 constexpr int kPairWaves = kPairThreads / 64;
 __device__ __forceinline__ void apply_pairs(
@@ -325,6 +328,7 @@ __device__ __forceinline__ void apply_pairs(
       const int64_t nn = n + 1 < N ? n + 1 : n;
       const double hx = f[nn], hy = f[N + nn], hz = f[2 * N + nn];
       const int en = seg[nn + 1];
+      double ag = 0.0;   // the segment's factor of g
 #pragma unroll 2
       for (; p < e; ++p) {
         const double4 s = X64[p];
@@ -333,13 +337,15 @@ __device__ __forceinline__ void apply_pairs(
         const double r = rsqrt_refined(d);                // (|r|^2 + eps^2)^(-1/2)
         const double wr = s.w * r;
         const double t = wr * (r * r);                    // w (|r|^2 + eps^2)^(-3/2)
-        const double rg = fma(rz, gz, fma(ry, gy, rx * gx));
-        const double al = fma(t, eps2, wr);               // (|r|^2 + 2 eps^2) t
-        const double be = t * rg;
-        ux = fma(al, gx, fma(be, rx, ux));
-        uy = fma(al, gy, fma(be, ry, uy));
-        uz = fma(al, gz, fma(be, rz, uz));
+        const double be = t * fma(rz, gz, fma(ry, gy, rx * gx));
+        ag += fma(t, eps2, wr);                           // (|r|^2 + 2 eps^2) t
+        ux = fma(be, rx, ux);
+        uy = fma(be, ry, uy);
+        uz = fma(be, rz, uz);
       }
+      ux = fma(ag, gx, ux);
+      uy = fma(ag, gy, uy);
+      uz = fma(ag, gz, uz);
       if (p >= b) break;
       n = n + 1;
       gx = hx;
