@@ -421,19 +421,18 @@ nrs_status nrs_lu_query(nrs_ctx* ctx, const void* ws, int32_t* flags);
  * FP32 and FP64 assembly kernels (rows per workgroup 64 / 128 / 256 x force
  * points per strip 4 / 8 / 16) on this problem (one warm-up launch, then the
  * best of three runs of eight back-to-back launches each, HIP events on the
- * context's stream), and records the fastest (none where the shape that an
- * untuned problem of this size gets is faster than all of them)
+ * context's stream), and records the fastest
  * for the problem's size class (floor(log2 N), floor(log2(Q / N))) in the
  * context; every later assembly of a problem of that class, in any entry
- * point, uses what was recorded.  Every shape computes each matrix entry with the same
+ * point, uses it.  Every shape computes each matrix entry with the same
  * operations, so tuning never changes a result.  Synchronises.  ws: at least
  * nrs_workspace_size(N, Q, M, NRS_FP32_IR) bytes.  out (host, may be NULL):
- * the fastest candidate and its timings. */
+ * the choice and its timings. */
 typedef struct {
   int32_t size_class;
   int32_t block32, strip32, block64, strip64;
   float ms32, ms64;                 /* tuned average per assembly, ms        */
-  float default_ms32, default_ms64; /* shape of 128 rows, 8 points           */
+  float default_ms32, default_ms64; /* shape of an untuned problem this size */
 } nrs_tune_result;
 nrs_status nrs_autotune(nrs_ctx* ctx, const nrs_problem* pb, void* ws, size_t ws_bytes,
                         nrs_tune_result* out);

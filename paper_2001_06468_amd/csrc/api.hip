@@ -978,6 +978,16 @@ int32_t asm_shape_for(const nrs_ctx* ctx, int64_t N, int64_t Q, int bits) {
   return -1;
 }
 
+void record_shapes(nrs_ctx* ctx, int32_t cls, int32_t shape32, int32_t shape64) {
+  for (auto& e : ctx->tune)
+    if (e.cls == cls) {
+      e.shape32 = shape32;
+      e.shape64 = shape64;
+      return;
+    }
+  ctx->tune.push_back({cls, shape32, shape64});
+}
+
 }  // namespace nrs
 
 extern "C" {
@@ -997,9 +1007,8 @@ nrs_status nrs_autotune(nrs_ctx* ctx, const nrs_problem* pb, void* ws, size_t ws
   hipEvent_t e0, e1;
   NRS_HIP(ctx, hipEventCreate(&e0));
   NRS_HIP(ctx, hipEventCreate(&e1));
-  int32_t best[2] = {kAsmDefaultShape, kAsmDefaultShape};
+  int32_t best[2] = {0, 0};
   float best_ms[2] = {0.f, 0.f}, def_ms[2] = {0.f, 0.f};
-  int32_t record[2] = {-1, -1};   // shape used from now on: the best, or the size's own
   hipError_t err = hipSuccess;
   // per shape: one warm-up launch, then the best of three timed runs of
   // kLaunches back-to-back launches (one event pair around each run, so that
@@ -1010,15 +1019,13 @@ nrs_status nrs_autotune(nrs_ctx* ctx, const nrs_problem* pb, void* ws, size_t ws
                      : launch_assemble<double>(*pb, sb.srt, sb.A64, sb.lda, s, shape);
   };
   for (int prec = 0; prec < 2 && err == hipSuccess; ++prec) {
-    // the candidates, then (shape kAsmShapes here) the untuned shape of this size
-    for (int shape = 0; shape <= kAsmShapes && err == hipSuccess; ++shape) {
-      const bool own = shape == kAsmShapes;
-      err = launch(prec, own ? -1 : shape);
+    const int32_t untuned = asm_untuned_shape(pb->N, prec == 0 ? 32 : 64);
+    for (int shape = 0; shape < kAsmShapes && err == hipSuccess; ++shape) {
+      err = launch(prec, shape);
       float avg = 0.f;
       for (int rep = 0; rep < 3 && err == hipSuccess; ++rep) {
         err = hipEventRecord(e0, s);
-        for (int k = 0; k < kLaunches && err == hipSuccess; ++k)
-          err = launch(prec, own ? -1 : shape);
+        for (int k = 0; k < kLaunches && err == hipSuccess; ++k) err = launch(prec, shape);
         if (err == hipSuccess) err = hipEventRecord(e1, s);
         if (err == hipSuccess) err = hipEventSynchronize(e1);
         float ms = 0.f;
@@ -1026,11 +1033,7 @@ nrs_status nrs_autotune(nrs_ctx* ctx, const nrs_problem* pb, void* ws, size_t ws
         const float per = ms / kLaunches;
         if (rep == 0 || per < avg) avg = per;
       }
-      if (own) {
-        record[prec] = avg < best_ms[prec] ? -1 : best[prec];
-        continue;
-      }
-      if (shape == kAsmDefaultShape) def_ms[prec] = avg;
+      if (shape == untuned) def_ms[prec] = avg;
       if (shape == 0 || avg < best_ms[prec]) {
         best_ms[prec] = avg;
         best[prec] = shape;
@@ -1041,14 +1044,7 @@ nrs_status nrs_autotune(nrs_ctx* ctx, const nrs_problem* pb, void* ws, size_t ws
   hipEventDestroy(e1);
   if (err != hipSuccess) return fail(ctx, NRS_E_HIP, std::string("autotune: ") + hipGetErrorString(err));
   const int32_t c = size_class(pb->N, pb->Q);
-  bool found = false;
-  for (auto& e : ctx->tune)
-    if (e.cls == c) {
-      e.shape32 = record[0];
-      e.shape64 = record[1];
-      found = true;
-    }
-  if (!found) ctx->tune.push_back({c, record[0], record[1]});
+  record_shapes(ctx, c, best[0], best[1]);
   if (out) {
     out->size_class = c;
     asm_shape_dims(best[0], &out->block32, &out->strip32);
@@ -1057,6 +1053,25 @@ nrs_status nrs_autotune(nrs_ctx* ctx, const nrs_problem* pb, void* ws, size_t ws
     out->ms64 = best_ms[1];
     out->default_ms32 = def_ms[0];
     out->default_ms64 = def_ms[1];
+  }
+  return NRS_OK;
+}
+
+// Not part of the library's interface: for tests.  set [2] (may be NULL): FP32 and FP64 launch
+// shapes of later assemblies of the size class of (N, Q), as nrs_autotune would record
+// them; dims [4]: rows and force points per workgroup that they get, FP32 then FP64.
+nrs_status nrs_internal_assembly_shape(nrs_ctx* ctx, int64_t N, int64_t Q, const int32_t* set,
+                                       int32_t* dims) {
+  if (!ctx || N <= 0 || Q <= 0 || !dims) return fail(ctx, NRS_E_ARG, "bad arguments");
+  if (set) {
+    if (set[0] < 0 || set[0] >= kAsmShapes || set[1] < 0 || set[1] >= kAsmShapes)
+      return fail(ctx, NRS_E_ARG, "no such launch shape");
+    record_shapes(ctx, size_class(N, Q), set[0], set[1]);
+  }
+  for (int k = 0; k < 2; ++k) {
+    const int bits = k == 0 ? 32 : 64;
+    const int32_t shape = asm_shape_for(ctx, N, Q, bits);
+    asm_shape_dims(shape < 0 ? asm_untuned_shape(N, bits) : shape, dims + 2 * k, dims + 2 * k + 1);
   }
   return NRS_OK;
 }

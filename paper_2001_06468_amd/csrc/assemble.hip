@@ -22,17 +22,11 @@ namespace {
 // autotuner) never changes a result.
 constexpr int kShapeBlk[kAsmShapes] = {64, 64, 64, 128, 128, 128, 256, 256, 256};
 constexpr int kShapeTN[kAsmShapes] = {4, 8, 16, 4, 8, 16, 4, 8, 16};
-// Shape of a problem that is not tuned, by force points: small matrices leave
-// SIMDs idle unless every strip is one force point (64 rows x 1 point, shape
-// kAsmShapes, not a candidate of the autotuner), the largest want few, long
-// workgroups.  Measured, us, FP32 / FP64, against 128 rows x 8 points: N = 40 3.3 /
-// 3.3 (12.2 / 13.2), N = 480 6.4 / 7.9 (15.3 / 16.8), N = 1000 13.1 / 18.6 (20.2 /
-// 27.2), N = 1920 64 x 1 34.1 / 56.0, 128 x 4 34.6 / 52.6 (36.0 / 61.4), N = 4000
-// 128 x 4 184 / 293, 256 x 4 172 / 296 (189 / 292).
-inline int asm_untuned_shape(int64_t N) {
-  if (N <= 1536) return kAsmShapes;
-  return N <= 3072 ? 3 : 6;
-}
+// In the smallest shape each of four waves takes one force point of the strip, in the
+// others every wave takes the whole strip for 64 rows of its own: small matrices leave SIMDs idle
+// unless a wave has one force point only.
+constexpr bool asm_split(int blk, int tn) { return blk == 64 && tn == 4; }
+constexpr int asm_threads(int blk, int tn) { return asm_split(blk, tn) ? 64 * tn : blk; }
 
 // Component j of e_i x r.
 __device__ inline double cross_unit(int i, int j, const double r[3]) {
@@ -107,27 +101,40 @@ __device__ inline void rigid_task(int64_t t, const RigidArgs& g, T* __restrict__
 }
 
 // Workgroups past the force-point strips (blockIdx.y >= strips) take the
-// rigid-body tasks, kAsmBlock consecutive tasks each.
+// rigid-body tasks, one consecutive task per thread.
 template <class T, int kAsmBlock, int kTN>
 __device__ inline bool rigid_part(const RigidArgs& g, T* __restrict__ A, int64_t lda) {
   const int64_t strips = (g.N + kTN - 1) / kTN;
   if ((int64_t)blockIdx.y < strips) return false;
-  const int64_t t = (((int64_t)blockIdx.y - strips) * gridDim.x + blockIdx.x) * kAsmBlock +
-                    threadIdx.x;
+  const int64_t t = (((int64_t)blockIdx.y - strips) * gridDim.x + blockIdx.x) *
+                        asm_threads(kAsmBlock, kTN) + threadIdx.x;
   if (g.M > 0) rigid_task<T>(t, g, A, lda);
   return true;
+}
+
+// Row of this thread and its force points [n0, nend).
+template <int kAsmBlock, int kTN>
+__device__ inline int64_t asm_share(int64_t N, int64_t& n0, int64_t& nend) {
+  n0 = (int64_t)blockIdx.y * kTN;
+  if (asm_split(kAsmBlock, kTN)) {
+    n0 += __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    nend = min<int64_t>(N, n0 + 1);
+    return blockIdx.x * (int64_t)kAsmBlock + (threadIdx.x & 63);
+  }
+  nend = min<int64_t>(N, n0 + kTN);
+  return blockIdx.x * (int64_t)kAsmBlock + threadIdx.x;
 }
 
 // FP32 form: coordinates carried as hi + lo floats so that r = x_m - X_q keeps
 // FP32 relative accuracy even when |r| << |x|.
 template <int kAsmBlock, int kTN>
-__global__ __launch_bounds__(kAsmBlock) void k_assemble32(
+__global__ __launch_bounds__(asm_threads(kAsmBlock, kTN)) void k_assemble32(
     int64_t N, const double* __restrict__ x, const int32_t* __restrict__ seg,
     const float4* __restrict__ Xhi, const float4* __restrict__ Xlo, float eps2, float scale,
     float* __restrict__ A, int64_t lda, RigidArgs rg) {
   if (rigid_part<float, kAsmBlock, kTN>(rg, A, lda)) return;
-  const int64_t m = blockIdx.x * (int64_t)kAsmBlock + threadIdx.x;
-  const int64_t n0 = (int64_t)blockIdx.y * kTN;
+  int64_t n0, nend;
+  const int64_t m = asm_share<kAsmBlock, kTN>(N, n0, nend);
   const bool live = m < N;
   float xh = 0, yh = 0, zh = 0, xl = 0, yl = 0, zl = 0;
   if (live) {
@@ -139,7 +146,6 @@ __global__ __launch_bounds__(kAsmBlock) void k_assemble32(
     yl = (float)(py - (double)yh);
     zl = (float)(pz - (double)zh);
   }
-  const int64_t nend = min<int64_t>(N, n0 + kTN);
   for (int64_t n = n0; n < nend; ++n) {
     const int a = seg[n], b = seg[n + 1];
     float a00 = 0, a11 = 0, a22 = 0, a01 = 0, a02 = 0, a12 = 0;
@@ -179,13 +185,13 @@ __global__ __launch_bounds__(kAsmBlock) void k_assemble32(
 }
 
 template <int kAsmBlock, int kTN>
-__global__ __launch_bounds__(kAsmBlock) void k_assemble64(
+__global__ __launch_bounds__(asm_threads(kAsmBlock, kTN)) void k_assemble64(
     int64_t N, const double* __restrict__ x, const int32_t* __restrict__ seg,
     const double4* __restrict__ X64, double eps2, double scale, double* __restrict__ A,
     int64_t lda, RigidArgs rg) {
   if (rigid_part<double, kAsmBlock, kTN>(rg, A, lda)) return;
-  const int64_t m = blockIdx.x * (int64_t)kAsmBlock + threadIdx.x;
-  const int64_t n0 = (int64_t)blockIdx.y * kTN;
+  int64_t n0, nend;
+  const int64_t m = asm_share<kAsmBlock, kTN>(N, n0, nend);
   const bool live = m < N;
   double px = 0, py = 0, pz = 0;
   if (live) {
@@ -193,7 +199,6 @@ __global__ __launch_bounds__(kAsmBlock) void k_assemble64(
     py = x[N + m];
     pz = x[2 * N + m];
   }
-  const int64_t nend = min<int64_t>(N, n0 + kTN);
   for (int64_t n = n0; n < nend; ++n) {
     const int a = seg[n], b = seg[n + 1];
     double a00 = 0, a11 = 0, a22 = 0, a01 = 0, a02 = 0, a12 = 0;
@@ -517,7 +522,8 @@ dim3 asm_grid(const nrs_problem& pb) {
   const int64_t N = pb.N, M = pb.M, n = 3 * N + 6 * M;
   const int64_t gx = (N + BLK - 1) / BLK, strips = (N + TN - 1) / TN;
   const int64_t tasks = 3 * N * M + n * M;
-  const int64_t extra = (tasks + gx * BLK - 1) / (gx * BLK);
+  const int64_t row = gx * asm_threads(BLK, TN);
+  const int64_t extra = (tasks + row - 1) / row;
   return dim3((unsigned)gx, (unsigned)(strips + extra));
 }
 inline RigidArgs rigid_args(const nrs_problem& pb, const Sorted& srt) {
@@ -527,7 +533,7 @@ template <int BLK, int TN>
 void asm32(const nrs_problem& pb, const Sorted& srt, float* A, int64_t lda, float scale,
            hipStream_t s) {
   const dim3 g = asm_grid<BLK, TN>(pb);
-  hipLaunchKernelGGL((k_assemble32<BLK, TN>), g, dim3(BLK), 0, s, pb.N, pb.x,
+  hipLaunchKernelGGL((k_assemble32<BLK, TN>), g, dim3(asm_threads(BLK, TN)), 0, s, pb.N, pb.x,
                      srt.seg, srt.X32hi, srt.X32lo, (float)(pb.eps * pb.eps), scale, A, lda,
                      rigid_args(pb, srt));
 }
@@ -535,7 +541,7 @@ template <int BLK, int TN>
 void asm64(const nrs_problem& pb, const Sorted& srt, double* A, int64_t lda, double scale,
            hipStream_t s) {
   const dim3 g = asm_grid<BLK, TN>(pb);
-  hipLaunchKernelGGL((k_assemble64<BLK, TN>), g, dim3(BLK), 0, s, pb.N, pb.x,
+  hipLaunchKernelGGL((k_assemble64<BLK, TN>), g, dim3(asm_threads(BLK, TN)), 0, s, pb.N, pb.x,
                      srt.seg, srt.X64, pb.eps * pb.eps, scale, A, lda, rigid_args(pb, srt));
 }
 
@@ -544,16 +550,15 @@ void asm_dispatch(int shape, const nrs_problem& pb, const Sorted& srt, T* A, int
                   hipStream_t s);
 #define NRS_ASM_CASES(F)                                                                        \
   switch (shape) {                                                                             \
-    case kAsmShapes: F<64, 1>(pb, srt, A, lda, scale, s); break;                               \
     case 0: F<64, 4>(pb, srt, A, lda, scale, s); break;                                        \
     case 1: F<64, 8>(pb, srt, A, lda, scale, s); break;                                        \
     case 2: F<64, 16>(pb, srt, A, lda, scale, s); break;                                       \
     case 3: F<128, 4>(pb, srt, A, lda, scale, s); break;                                       \
+    case 4: F<128, 8>(pb, srt, A, lda, scale, s); break;                                       \
     case 5: F<128, 16>(pb, srt, A, lda, scale, s); break;                                      \
     case 6: F<256, 4>(pb, srt, A, lda, scale, s); break;                                       \
     case 7: F<256, 8>(pb, srt, A, lda, scale, s); break;                                       \
-    case 8: F<256, 16>(pb, srt, A, lda, scale, s); break;                                      \
-    default: F<128, 8>(pb, srt, A, lda, scale, s); break;                                      \
+    default: F<256, 16>(pb, srt, A, lda, scale, s); break;                                     \
   }
 template <>
 void asm_dispatch<float>(int shape, const nrs_problem& pb, const Sorted& srt, float* A,
@@ -569,8 +574,22 @@ void asm_dispatch<double>(int shape, const nrs_problem& pb, const Sorted& srt, d
 
 }  // namespace
 
+// Shape of a problem that is not tuned.  Small matrices need every wave they can get,
+// large ones long stores.  Measured, us per nrs_assemble call with 10 quadrature points per
+// force point, 64 x 4 / 128 x 4 / 256 x 4 (best of the other six):
+//   FP32 N = 40: 10.6 / 16.0 / 16.7 (22.2); 1000: 24.2 / 25.1 / 25.7 (29.9); 1500: 35.8 / 34.3 /
+//   35.2 (37.3); 2100: 50.7 / 48.4 / 50.3 (52.9); 3100: 111 / 96 / 94 (100); 4500: 303 / 268 /
+//   236 (244); 6000: 429 / 375 / 363 (370); 8000: 700 / 637 / 628 (635)
+//   FP64 N = 40: 11.2 / 18.2 / 18.9 (24.6); 1000: 28.5 / 30.7 / 31.7 (36.2); 2100: 78 / 80 / 78
+//   (87); 3100: 209 / 214 / 198 (206); 4500: 435 / 399 / 373 (379); 5200: 477 / 462 / 470 (465);
+//   6000: 627 / 607 / 615 (608); 8000: 1084 / 1063 / 1076 (1061)
+int32_t asm_untuned_shape(int64_t N, int) {
+  if (N <= 1536) return 0;
+  if (N <= 3072) return 3;
+  return 6;
+}
+
 void asm_shape_dims(int32_t shape, int32_t* blk, int32_t* tn) {
-  if (shape < 0 || shape >= kAsmShapes) shape = kAsmDefaultShape;
   *blk = kShapeBlk[shape];
   *tn = kShapeTN[shape];
 }
@@ -583,7 +602,7 @@ hipError_t launch_assemble(const nrs_problem& pb, const Sorted& srt, T* A, int64
   const T scale = (T)(1.0 / (8.0 * kPi * pb.mu));
   // one launch: the fused operator and, in extra workgroups, the rigid-body
   // rows and columns
-  if (shape < 0) shape = asm_untuned_shape(N);
+  if (shape < 0) shape = asm_untuned_shape(N, 8 * (int)sizeof(T));
   if (N > 0) asm_dispatch<T>(shape, pb, srt, A, lda, scale, s);
   (void)n;
   return hipGetLastError();

@@ -500,7 +500,7 @@ hipError_t launch_build_csr(int64_t N, int64_t Q, const double* X, const double*
 // Assembly launch shapes: shape index -> (rows per workgroup, force points
 // per strip); -1 = by the problem's size.  Results do not depend on the shape.
 constexpr int kAsmShapes = 9;
-constexpr int kAsmDefaultShape = 4;   // 128 rows, 8 force points (the autotuner's yardstick)
+int32_t asm_untuned_shape(int64_t N, int bits);   // bits: 32 or 64
 void asm_shape_dims(int32_t shape, int32_t* blk, int32_t* tn);
 template <class T>
 hipError_t launch_assemble(const nrs_problem& pb, const Sorted& srt, T* A, int64_t lda,
