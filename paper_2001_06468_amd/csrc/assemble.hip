@@ -583,9 +583,9 @@ void asm_dispatch<double>(int shape, const nrs_problem& pb, const Sorted& srt, d
 //   FP64 N = 40: 11.2 / 18.2 / 18.9 (24.6); 1000: 28.5 / 30.7 / 31.7 (36.2); 2100: 78 / 80 / 78
 //   (87); 3100: 209 / 214 / 198 (206); 4500: 435 / 399 / 373 (379); 5200: 477 / 462 / 470 (465);
 //   6000: 627 / 607 / 615 (608); 8000: 1084 / 1063 / 1076 (1061)
-int32_t asm_untuned_shape(int64_t N, int) {
+int32_t asm_untuned_shape(int64_t N, int bits) {
   if (N <= 1536) return 0;
-  if (N <= 3072) return 3;
+  if (N <= 3072 || (bits == 64 && N > 5000)) return 3;
   return 6;
 }
 

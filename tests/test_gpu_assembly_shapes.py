@@ -80,3 +80,18 @@ def test_tuner_reports_the_shape_in_use(name):
             assert r[f"ms{bits}"] == r[f"default_ms{bits}"]
     nrs.nrs_autotune_clear(ctx)
     assert _shape(ctx, pb) == untuned
+
+
+def test_untuned_shapes_by_size():
+    """Both sides of the lines between the untuned shapes (no launch)."""
+    ctx = nrs.Context(0)
+
+    class Size:
+        def __init__(self, N):
+            self.N, self.Q = N, 10 * N
+
+    for N, want in [(1, ((64, 4), (64, 4))), (1536, ((64, 4), (64, 4))),
+                    (1537, ((128, 4), (128, 4))), (3072, ((128, 4), (128, 4))),
+                    (3073, ((256, 4), (256, 4))), (5000, ((256, 4), (256, 4))),
+                    (5001, ((256, 4), (128, 4))), (80000, ((256, 4), (128, 4)))]:
+        assert _shape(ctx, Size(N)) == want, N
