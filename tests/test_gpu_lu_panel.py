@@ -143,3 +143,69 @@ def test_panel_zero_column_with_a_nan_is_singular(ctx, dtype, row):
     _, ipiv, _, sing = _factor(ctx, A0, dtype)
     assert sing == 1
     np.testing.assert_array_equal(ipiv[:20], np.arange(20))
+
+
+# panels lose 64 rows at a time, so a shape's largest height occurs only if the order is that height
+@pytest.mark.parametrize("n", [1024, 1536, 2048, 3072, 4096, 8192])
+def test_panel_shapes_fp64_at_their_last_row(ctx, n):
+    A0 = np.random.default_rng(n).normal(size=(n, n))
+    LU, ipiv, perm, sing = _factor(ctx, A0, torch.float64)
+    assert sing == 0
+    np.testing.assert_array_equal(ipiv, scipy.linalg.lu_factor(A0)[1])
+    assert _backward_ok(A0, LU, perm, 2.0 ** -53)
+
+
+@pytest.mark.parametrize("n", [512, 1024, 3073, 4097])
+def test_panel_shapes_fp32_wide(ctx, n):
+    """FP32 in every rows-per-thread / width shape.  A pivot is the largest of its column
+    as this elimination computed it: no multiplier is larger than one."""
+    A0 = np.random.default_rng(n).normal(size=(n, n)).astype(np.float32)
+    LU, ipiv, perm, sing = _factor(ctx, A0, torch.float32, pad=1)
+    assert sing == 0
+    assert ((ipiv >= np.arange(n)) & (ipiv < n)).all()
+    assert float(torch.tril(LU, -1).abs().max()) <= 1.0
+    assert _backward_ok(A0, LU, perm, 2.0 ** -24)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_panel_pivots_on_exact_arithmetic(ctx, dtype):
+    """P A = L U with L of eighths and U of small integers, a power of two on the
+    diagonal: every step is exact in either precision, so pivots and factors are those
+    that built the matrix."""
+    n = 700
+    rng = np.random.default_rng(12)
+    L = np.tril(rng.integers(-7, 8, size=(n, n)) / 8.0 * (rng.random((n, n)) < 0.02), -1) + np.eye(n)
+    U = np.triu(rng.integers(-4, 5, size=(n, n)) * (rng.random((n, n)) < 0.02), 1).astype(float)
+    U += np.diag(2.0 ** rng.integers(0, 3, size=n))
+    A0 = L @ U
+    swap = rng.permutation(n)
+    LU, ipiv, perm, sing = _factor(ctx, A0[swap], dtype)
+    assert sing == 0
+    np.testing.assert_array_equal(swap[perm.cpu().numpy()], np.arange(n))
+    np.testing.assert_array_equal(LU.cpu().double().numpy(), np.tril(L, -1) + U)
+    # the interchanges lead to the same permutation
+    at = np.arange(n)
+    for j, p in enumerate(ipiv):
+        at[[j, p]] = at[[p, j]]
+    np.testing.assert_array_equal(at, perm.cpu().numpy())
+
+
+@pytest.mark.parametrize("dtype,scales", [(torch.float64, [2.0 ** -960, 1.0, 2.0 ** 960]),
+                                          (torch.float32, [2.0 ** -100, 1.0, 2.0 ** 100])])
+def test_panel_pivots_outside_the_plain_range(ctx, dtype, scales):
+    """Columns scaled so that pivots lie on both sides of the range in which a quotient is
+    formed by the reciprocal.  Scaling a column by a power of two scales that column of U
+    and changes nothing else, as long as nothing leaves the normal numbers."""
+    n = 200
+    rng = np.random.default_rng(13)
+    A0 = rng.normal(size=(n, n))
+    if dtype == torch.float32:
+        A0 = A0.astype(np.float32)
+    c = rng.choice(scales, size=n)
+    ref, ip0, _, _ = _factor(ctx, A0, dtype)
+    LU, ipiv, perm, sing = _factor(ctx, A0 * c, dtype)
+    assert sing == 0
+    np.testing.assert_array_equal(ipiv, ip0)
+    got, ref = LU.cpu().double().numpy(), ref.cpu().double().numpy()
+    np.testing.assert_array_equal(np.tril(got, -1), np.tril(ref, -1))
+    np.testing.assert_array_equal(np.triu(got) / c, np.triu(ref))
