@@ -183,6 +183,9 @@ __global__ __launch_bounds__(kCoopThreads) void k_getf2_coop(int64_t n, int64_t 
           best = s_v[w];
           bi = s_i[w];
         }
+      // none but NaN here: row n stands for no candidate, except that the diagonal row
+      // stays in the running, so that a column without any number keeps it
+      if (bi == n && gj >= r0 && gj < r0 + nr) bi = gj;
       slot[0] = best;
       slot[1] = (double)bi;
       s_p = bi;
@@ -264,7 +267,7 @@ __global__ __launch_bounds__(kCoopThreads) void k_getf2_coop(int64_t n, int64_t 
     }
     __syncthreads();
     const T piv = s_prow[j];
-    if (piv == T(0)) {
+    if (piv == T(0) || piv != piv) {
       if (g == 0 && tid == 0) atomicOr(sing, 1);
       continue;
     }

@@ -209,3 +209,15 @@ def test_panel_pivots_outside_the_plain_range(ctx, dtype, scales):
     got, ref = LU.cpu().double().numpy(), ref.cpu().double().numpy()
     np.testing.assert_array_equal(np.tril(got, -1), np.tril(ref, -1))
     np.testing.assert_array_equal(np.triu(got) / c, np.triu(ref))
+
+
+def test_nan_column_stays_in_range_past_the_register_panel(ctx):
+    """The same for panels of more rows than the registers of a workgroup hold."""
+    n = 8260
+    A0 = np.random.default_rng(14).normal(size=(n, n))
+    A0[:, 20] = np.nan
+    LU, ipiv, perm, sing = _factor(ctx, A0, torch.float64)
+    assert sing == 1
+    assert ((ipiv >= np.arange(n)) & (ipiv < n)).all()
+    np.testing.assert_array_equal(np.sort(perm.cpu().numpy()), np.arange(n))
+    assert bool(torch.isfinite(LU[:, :20]).all()) and bool(torch.isnan(LU[20, 20]))
