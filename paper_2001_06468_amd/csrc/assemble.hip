@@ -279,13 +279,14 @@ __global__ void k_rhs_batch(const BatchSys* __restrict__ sys, const int64_t* __r
 // order.
 // What bounds it: FP64 issue (24 instructions and a quarter-rate reciprocal square
 // root per pair, 3 per segment), and below about 10^7 pairs the launch and the scalar
-// loads' latency, hence the short chunks of apply_plan().  The factor of a segment's force
-// density is summed over the segment and applied once: applied pair by pair, 26
-// instructions, 13,000 x 130,000 pairs took 1687 us a call (1600 us so; 1615 us with gathered
-// records); only segments of one or two points lose by it (4000 of one: 34.8 -> 36.6 us).  Against gathering
-// 64-byte source records first and the tracers' chunks of 256 sources (mean over calls, converged
-// ones that exit included): one filament (40 x 400 pairs) 16.5 -> 5.7 us, 25 filaments
-// (1000 x 10,000) 21.6 -> 13.8 us, 100 filaments (4000 x 40,000) 100.8 -> 99.8 us.
+// loads' latency, hence the short chunks of apply_plan().  The factor of a segment's
+// force density is summed over the segment and applied once: applied pair by pair, 26
+// instructions, 13,000 x 130,000 pairs took 1687 us a call (1600 us so; 1615 us with
+// gathered records); only segments of one or two points lose by it (4000 of one point:
+// 34.8 -> 36.6 us).  Against gathering 64-byte source records first and the tracers'
+// chunks of 256 sources (mean over calls, converged ones that exit included): one
+// filament (40 x 400 pairs) 16.5 -> 5.7 us, 25 filaments (1000 x 10,000) 21.6 -> 13.8
+// us, 100 filaments (4000 x 40,000) 100.8 -> 99.8 us.
 constexpr int kPairThreads = 256;
 constexpr int kPairWaves = kPairThreads / 64;
 __device__ __forceinline__ void apply_pairs(
@@ -659,8 +660,8 @@ hipError_t launch_apply(const nrs_problem& pb, const Sorted& srt, const double* 
     const FieldPlan fp = apply_plan(N, Q);
     if (fp.chunks > chunks) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_apply_pairs, dim3((unsigned)pair_blocks(fp.pblocks, fp.chunks)),
-                       dim3(kPairThreads), 0, s, N, fp.pblocks, fp.chunks, fp.chunk, pb.x, srt.seg, srt.nus, srt.X64, v,
-                       pb.eps * pb.eps, part, stop);
+                       dim3(kPairThreads), 0, s, N, fp.pblocks, fp.chunks, fp.chunk, pb.x, srt.seg,
+                       srt.nus, srt.X64, v, pb.eps * pb.eps, part, stop);
     const unsigned blocks = (unsigned)((3 * N + 63) / 64 + pb.M);
     hipLaunchKernelGGL(k_apply_stage2, dim3(blocks), dim3(kApplyThreads), 0, s, N, pb.M,
                        fp.chunks, part, 1.0 / (8.0 * kPi * pb.mu), pb.x, pb.body, pb.Y, srt.W, v,

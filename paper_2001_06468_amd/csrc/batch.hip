@@ -7,7 +7,8 @@
 // What bounds it: of 27.7 ms for 96 systems of orders 300..6000 the LU takes 21.7, the
 // assemblies on four streams about 1, four triangular passes 1.6 and the FP64 products 2.
 // With every pass but the LU and the triangular ones launched per system (about 2200
-// short launches) the same batch took 32.4 ms (28.6 ms in one launch a pass, with the LU then at 22.5).
+// short launches) the same batch took 32.4 ms (28.6 ms in one launch a pass, with the
+// LU then at 22.5).
 #include <algorithm>
 #include <cmath>
 #include <cstring>

@@ -21,7 +21,9 @@
 // broadcast of the pivot row, R fused updates per column left.
 // Pivots and factors are those of the column-by-column elimination (largest
 // magnitude, lowest row on ties; every entry takes its updates in increasing
-// pivot order; multipliers are correctly rounded quotients).
+// pivot order; multipliers are correctly rounded quotients, except that of an entry so small
+// (below about 1e-291 in FP64, 2e-31 in FP32) that its remainder is subnormal, which
+// may be off by one more rounding).
 //
 // Measured, FP64, per launch of W columns: 19.9 us (W = 16) at 512 rows, 21.9 us
 // at 1024, 24.1 us at 1536, 12.7 us (W = 8) at 2048, 15.5 us at 3072, 19.0 us at
@@ -103,9 +105,9 @@ __device__ inline double lane_value(double v, int lane) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// |piv| (hi: its high word) far enough from the ends of the range that 1/piv and the
-// remainder of the corrected quotient below are normal numbers: about 1e-279 to
-// 1e279 in FP64, 1e-29 to 1e29 in FP32
+// |piv| (hi: its high word) far enough from the ends of the range that 1/piv is a normal
+// number and the corrected quotient below can neither overflow nor lose the reciprocal's
+// accuracy: about 1e-279 to 1e279 in FP64, 1e-29 to 1e29 in FP32
 template <class T>
 __device__ inline bool plain_pivot(uint32_t hi);
 template <>
@@ -366,8 +368,8 @@ __device__ inline void eliminate_column(PanelLds<T, W>& S, T (&a)[R][W], int& po
   // One path for all columns: with the update on one side of a branch only, the whole
   // of a[][] was copied to other registers and back for each column.
   if (plain_pivot<T>((uint32_t)khi)) {
-    // quotient by the reciprocal, corrected by its remainder: the correctly
-    // rounded quotient
+    // quotient by the reciprocal, corrected by its remainder: correctly rounded
+    // where the remainder is a normal number (or zero)
     const T inv = T(1) / piv;
 #pragma unroll
     for (int r = 0; r < R; ++r) {

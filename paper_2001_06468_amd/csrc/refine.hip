@@ -71,8 +71,9 @@ __global__ void k_solve_begin_batch(const BatchSys* __restrict__ sys,
 // thread sums 16 bytes of rows over its workgroup's columns, four columns of loads in
 // flight, into part[chunk][row]; stage 2: per-row sum of the chunks in order and the
 // maximum over the rows, combined across workgroups as an integer maximum of its
-// bits (non-negative, never a NaN) in st->anorm, zeroed by stage 1.  Bound by HBM: 635 MB (FP32, n = 12,600) 400 us at one row and one load per
-// thread, 165 us (3.85 TB/s) so.
+// bits (non-negative, never a NaN) in st->anorm, zeroed by stage 1.  Bound by HBM:
+// 635 MB (FP32, n = 12,600) 400 us at one row and one load per thread, 165 us
+// (3.85 TB/s) so.
 constexpr int kSumThreads = 64, kMaxThreads = 256;
 template <class T>
 __device__ __forceinline__ void rowsum(int64_t bx, int64_t by, int64_t n,
@@ -454,7 +455,8 @@ static hipError_t anorm(int64_t n, const T* A, int64_t lda, SolveState* st, doub
   hipLaunchKernelGGL(k_rowsum<T>, dim3((unsigned)((n + kSumThreads * V - 1) / (kSumThreads * V)),
                                        (unsigned)chunks),
                      dim3(kSumThreads), 0, s, n, A, lda, cw, scratch, st);
-  hipLaunchKernelGGL(k_rowsum_max, grid1(n, kMaxThreads), dim3(kMaxThreads), 0, s, n, chunks, scratch, st);
+  hipLaunchKernelGGL(k_rowsum_max, grid1(n, kMaxThreads), dim3(kMaxThreads), 0, s, n, chunks,
+                     scratch, st);
   return hipGetLastError();
 }
 
@@ -570,7 +572,8 @@ hipError_t launch_rk_combine(int32_t M, double* Y, const double* K1, const doubl
 hipError_t launch_solve_begin(SolveState* st, int32_t method, int32_t* a, int64_t na, int32_t* b,
                               int64_t nb, hipStream_t s) {
   const int64_t m = std::max<int64_t>(1, std::max(na, nb));
-  hipLaunchKernelGGL(k_solve_begin, grid1(m, kBeginThreads), dim3(kBeginThreads), 0, s, st, method, a, na, b, nb);
+  hipLaunchKernelGGL(k_solve_begin, grid1(m, kBeginThreads), dim3(kBeginThreads), 0, s, st,
+                     method, a, na, b, nb);
   return hipGetLastError();
 }
 
