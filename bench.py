@@ -36,10 +36,10 @@ PEAK_FP64_TFLOPS = 78.6
 # HBM bytes per launch of the tile LU at n = 3150 from the FETCH_SIZE and
 # WRITE_SIZE counter runs (calibrated against a 256 MiB copy), valid only for
 # the kernel source they were taken on (first 16 hex digits of its SHA-256).
-LU_TRAFFIC = {"source_sha256_16": "ac86c9aaff497af9", "bytes_per_launch": 909496904, "n": 3150}
+LU_TRAFFIC = {"source_sha256_16": "cf99d1a5beefbd43", "bytes_per_launch": 817133056, "n": 3150}
 # HBM bytes per nrs_field_velocity call (sources + pair sum + chunk sum) on the
 # tracer workload, from the same two counter runs, valid for that field.hip.
-FIELD_TRAFFIC = {"source_sha256_16": "7f18d8d2f998ad7c", "bytes_per_call": 24459390, "Q": 73248,
+FIELD_TRAFFIC = {"source_sha256_16": "3d76b234acd80ef2", "bytes_per_call": 24468582, "Q": 73248,
                  "tracers": 806}
 
 
@@ -47,13 +47,13 @@ FIELD_TRAFFIC = {"source_sha256_16": "7f18d8d2f998ad7c", "bytes_per_call": 24459
 # scaled by what it reads for a kernel of known work run in the same
 # process), valid only for the kernel source they were taken on.
 COUNTERS = {
-    "lu": {"source": "lu_tiles.hip", "source_sha256_16": "ac86c9aaff497af9", "n": 3150,
-           "mfma_flops_per_launch": 2.202e10, "mfma_busy": 0.093,
-           "calibration": "FP32 4096^3 matrix product: 0.954 busy at 150 TFLOP/s"},
-    "assembly": {"source": "assemble.hip", "source_sha256_16": "cd14792605c821f9", "N": 1000,
+    "lu": {"source": "lu_tiles.hip", "source_sha256_16": "cf99d1a5beefbd43", "n": 3150,
+           "mfma_flops_per_launch": 2.202e10, "mfma_busy": 0.105,
+           "calibration": "FP32 4096^3 matrix product: 0.958 busy at 150 TFLOP/s"},
+    "assembly": {"source": "assemble.hip", "source_sha256_16": "cf75f7168377875a", "N": 1000,
                  "Q": 10000, "valu_fp32_flops_per_call": 4.061e8,
-                 "fp32_rsqrt_per_call": 1.05e7, "valu_fp64_flops_per_call": 6.517e8,
-                 "fp64_transcendental_per_call": 2.05e7,
+                 "fp32_rsqrt_per_call": 1.05e7, "valu_fp64_flops_per_call": 4.265e8,
+                 "fp64_transcendental_per_call": 1.02e7,
                  "calibration": "elementwise multiplies of 2^26 elements read 2^20: x 64"},
 }
 
