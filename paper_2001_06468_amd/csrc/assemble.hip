@@ -10,6 +10,7 @@
 // the segmented reduction over nu needs no cross-lane traffic and the dense
 // 3N x 3Q stokeslet matrix is never formed.
 #include <algorithm>
+#include <type_traits>
 
 #include "nrs_internal.h"
 
@@ -280,15 +281,19 @@ __global__ void k_rhs_batch(const BatchSys* __restrict__ sys, const int64_t* __r
 // What bounds it: FP64 issue (24 instructions and a quarter-rate reciprocal square
 // root per pair, 3 per segment), and below about 10^7 pairs the launch and the scalar
 // loads' latency, hence the short chunks of apply_plan().  The factor of a segment's
-// force density is summed over the segment and applied once: applied pair by pair, 26
-// instructions, 13,000 x 130,000 pairs took 1687 us a call (1600 us so; 1615 us with
-// gathered records); only segments of one or two points lose by it (4000 of one point:
-// 34.8 -> 36.6 us).  Against gathering 64-byte source records first and the tracers'
+// force density is summed over the segment and applied once (kPerSegment): applied pair by
+// pair, 26 instructions, 13,000 x 130,000 pairs took 1687 us a call (1600 us so; 1615 us
+// with gathered records).  Segments of one or two points lose by it (4000 of one point
+// 34.8 -> 36.6 us, of two 46.9 -> 48.4 us, of four 75.4 -> 74.9 us), hence the rule
+// pair_per_segment().  Against gathering 64-byte source records first and the tracers'
 // chunks of 256 sources (mean over calls, converged ones that exit included): one
 // filament (40 x 400 pairs) 16.5 -> 5.7 us, 25 filaments (1000 x 10,000) 21.6 -> 13.8
 // us, 100 filaments (4000 x 40,000) 100.8 -> 99.8 us.
 constexpr int kPairThreads = 256;
 constexpr int kPairWaves = kPairThreads / 64;
+__host__ __device__ inline bool pair_per_segment(int64_t N, int64_t Q) { return Q >= 4 * N; }
+
+template <bool kPerSegment>
 __device__ __forceinline__ void apply_pairs(
     int64_t block, int64_t N, int64_t pblocks, int32_t chunks, int64_t chunk,
     const double* __restrict__ x, const int32_t* __restrict__ seg,
@@ -334,7 +339,7 @@ __device__ __forceinline__ void apply_pairs(
       const int64_t nn = n + 1 < N ? n + 1 : n;
       const double hx = f[nn], hy = f[N + nn], hz = f[2 * N + nn];
       const int en = seg[nn + 1];
-      double ag = 0.0;   // the segment's factor of g
+      double ag = 0.0;   // the segment's factor of g (kPerSegment)
 #pragma unroll 2
       for (; p < e; ++p) {
         const double4 s = X64[p];
@@ -344,14 +349,23 @@ __device__ __forceinline__ void apply_pairs(
         const double wr = s.w * r;
         const double t = wr * (r * r);                    // w (|r|^2 + eps^2)^(-3/2)
         const double be = t * fma(rz, gz, fma(ry, gy, rx * gx));
-        ag += fma(t, eps2, wr);                           // (|r|^2 + 2 eps^2) t
+        const double al = fma(t, eps2, wr);               // (|r|^2 + 2 eps^2) t
         ux = fma(be, rx, ux);
         uy = fma(be, ry, uy);
         uz = fma(be, rz, uz);
+        if (kPerSegment) {
+          ag += al;
+        } else {
+          ux = fma(al, gx, ux);
+          uy = fma(al, gy, uy);
+          uz = fma(al, gz, uz);
+        }
       }
-      ux = fma(ag, gx, ux);
-      uy = fma(ag, gy, uy);
-      uz = fma(ag, gz, uz);
+      if (kPerSegment) {
+        ux = fma(ag, gx, ux);
+        uy = fma(ag, gy, uy);
+        uz = fma(ag, gz, uz);
+      }
       if (p >= b) break;
       n = n + 1;
       gx = hx;
@@ -372,13 +386,14 @@ __device__ __forceinline__ void apply_pairs(
   }
 }
 
+template <bool kPerSegment>
 __global__ __launch_bounds__(kPairThreads) void k_apply_pairs(
     int64_t N, int64_t pblocks, int32_t chunks, int64_t chunk, const double* __restrict__ x,
     const int32_t* __restrict__ seg, const int32_t* __restrict__ nus,
     const double4* __restrict__ X64, const double* __restrict__ f, double eps2,
     double* __restrict__ part, const int32_t* __restrict__ stop) {
   if (stop && *stop) return;
-  apply_pairs(blockIdx.x, N, pblocks, chunks, chunk, x, seg, nus, X64, f, eps2, part);
+  apply_pairs<kPerSegment>(blockIdx.x, N, pblocks, chunks, chunk, x, seg, nus, X64, f, eps2, part);
 }
 
 __global__ __launch_bounds__(kPairThreads) void k_apply_pairs_batch(
@@ -388,8 +403,16 @@ __global__ __launch_bounds__(kPairThreads) void k_apply_pairs_batch(
   const int32_t s = batch_find(first, s0, s1, g);
   const BatchSys& y = sys[s];
   if (!force && as_global(y.st)->stop) return;
-  apply_pairs(g - first[s], y.N, y.pblocks, y.chunks, y.chunk, as_global(y.x), as_global(y.seg),
-              as_global(y.nus), as_global(y.X64), as_global(y.sol), y.eps2, as_global(y.part));
+  const auto pairs = [&](auto per) {
+    apply_pairs<decltype(per)::value>(g - first[s], y.N, y.pblocks, y.chunks, y.chunk,
+                                      as_global(y.x), as_global(y.seg), as_global(y.nus),
+                                      as_global(y.X64), as_global(y.sol), y.eps2,
+                                      as_global(y.part));
+  };
+  if (pair_per_segment(y.N, y.Q))
+    pairs(std::true_type{});
+  else
+    pairs(std::false_type{});
 }
 
 constexpr int kApplyThreads = 1024, kApplyWaves = kApplyThreads / 64;
@@ -659,9 +682,10 @@ hipError_t launch_apply(const nrs_problem& pb, const Sorted& srt, const double* 
   if (N > 0) {
     const FieldPlan fp = apply_plan(N, Q);
     if (fp.chunks > chunks) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_apply_pairs, dim3((unsigned)pair_blocks(fp.pblocks, fp.chunks)),
-                       dim3(kPairThreads), 0, s, N, fp.pblocks, fp.chunks, fp.chunk, pb.x, srt.seg,
-                       srt.nus, srt.X64, v, pb.eps * pb.eps, part, stop);
+    hipLaunchKernelGGL(pair_per_segment(N, Q) ? k_apply_pairs<true> : k_apply_pairs<false>,
+                       dim3((unsigned)pair_blocks(fp.pblocks, fp.chunks)), dim3(kPairThreads), 0, s,
+                       N, fp.pblocks, fp.chunks, fp.chunk, pb.x, srt.seg, srt.nus, srt.X64, v,
+                       pb.eps * pb.eps, part, stop);
     const unsigned blocks = (unsigned)((3 * N + 63) / 64 + pb.M);
     hipLaunchKernelGGL(k_apply_stage2, dim3(blocks), dim3(kApplyThreads), 0, s, N, pb.M,
                        fp.chunks, part, 1.0 / (8.0 * kPi * pb.mu), pb.x, pb.body, pb.Y, srt.W, v,

@@ -1,8 +1,8 @@
 """Matrix-free product over segments of every length: force points without quadrature
-points, with one, with more than a wave's share, and chunks and waves that start inside a
-segment.  Against the sum over all pairs in NumPy; each side adds Q terms, of a few
-roundings each, so they differ by at most 2 (Q + 32) 2^-53 times the sum of the terms'
-magnitudes."""
+points, with one, with more than a wave's share, chunks and waves that start inside a
+segment, and both sides of four quadrature points per force point, where the sum changes
+form.  Against the sum over all pairs in NumPy; each side adds Q terms, of a few roundings
+each, so they differ by at most 2 (Q + 32) 2^-53 times the sum of the terms' magnitudes."""
 import numpy as np
 import pytest
 import torch
@@ -16,7 +16,7 @@ if torch.cuda.is_available():
 
 @pytest.mark.parametrize("N,Q,kind", [(1, 1, "all"), (3, 2, "all"), (70, 70, "all"),
                                       (65, 130, "sparse"), (40, 1537, "sparse"), (130, 900, "one"),
-                                      (200, 5000, "all")])
+                                      (200, 5000, "all"), (50, 199, "all"), (50, 200, "all")])
 def test_apply_segments(N, Q, kind):
     rng = np.random.default_rng(N + Q)
     nu = {"all": np.arange(Q) % N,
