@@ -49,8 +49,8 @@ FIELD_TRAFFIC = {"source_sha256_16": "3d76b234acd80ef2", "bytes_per_call": 24468
 COUNTERS = {
     "lu": {"source": "lu_tiles.hip", "source_sha256_16": "cf99d1a5beefbd43", "n": 3150,
            "mfma_flops_per_launch": 2.202e10, "mfma_busy": 0.105,
-           "calibration": "FP32 4096^3 matrix product: 0.958 busy at 150 TFLOP/s"},
-    "assembly": {"source": "assemble.hip", "source_sha256_16": "cf75f7168377875a", "N": 1000,
+           "calibration": "FP32 4096^3 matrix product: 0.953 busy at 150 TFLOP/s"},
+    "assembly": {"source": "assemble.hip", "source_sha256_16": "9404ed799f6965f9", "N": 1000,
                  "Q": 10000, "valu_fp32_flops_per_call": 4.061e8,
                  "fp32_rsqrt_per_call": 1.05e7, "valu_fp64_flops_per_call": 4.265e8,
                  "fp64_transcendental_per_call": 1.02e7,
